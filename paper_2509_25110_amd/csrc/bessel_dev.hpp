@@ -55,36 +55,80 @@ constexpr double kXDebye = 64.0;
 // and j_l(x) = sqrt(pi / (2 x)) J_nu(x).  With q = sqrt(nu^2 - x^2) = nu tanh a
 // and s = q / nu this is
 //   j_l(x) = e^eta S / (2 sqrt(x q)),  S = 1 + sum_{k=1..10} u_k(nu/q) / nu^k,
-// eta = -nu (atanh s - s): for s <= 0.7 from the series s^3 sum_m s^(2m)/(2m+3)
-// (no cancellation), above from q - nu log((nu + q) / x).  Along the band edge
-// nu s^3 stays near 60..150, where the ten terms leave a relative truncation
-// error below ~1e-16 for every x >= 20.
-__host__ __device__ inline double debye_j(int l, double x) {
-  const double nu = (double)l + 0.5;
-  const double q = sqrt((nu - x) * (nu + x));
-  const double s = q / nu;
-  double eta;
-  if (s <= 0.7) {
-    const double s2 = s * s;
-    double f = kEtaC[kEtaTerms - 1];
-#pragma unroll 1
-    for (int m = kEtaTerms - 2; m >= 0; --m) f = fma(f, s2, kEtaC[m]);
-    eta = -nu * (s * s2 * f);
-  } else {
-    eta = q - nu * log((nu + q) / x);
+// eta = -nu (atanh s - s).  atanh s = 2 atanh s' at s' = tanh(a / 2) = q / (nu + x), so with
+// y' = s'^2 = (nu - x) / (nu + x) and atanh s' - s' = s'^3 f(y') (f from debye_coef.hpp)
+//   eta = -y' (2 nu s' f(y') + q),
+// a sum of positive terms (no cancellation) for which a short polynomial is enough: y' <=
+// 0.40 at and 16 rows above the band edge for x >= kXDebye, within kEtaYMax.  Along the band
+// edge nu s^3 stays near 60..150, where the ten terms leave a relative truncation error
+// below ~1e-16 for every x >= 20.
+// N values j_l .. j_{l+N-1} go together, term by term, so that their chains overlap; ix =
+// 1 / x.  The polynomials are unrolled: as rolled loops (60 terms of the plain series of
+// atanh s - s, 65 of the u_k) every term waited for a load of its coefficient, and the seeds
+// were 20 % of a whole FP64 projection.  On the device their coefficients come by scalar
+// loads (coef): as literals the compiler keeps them in vector registers across the
+// callers' loops and copies one before every product.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) double *coef_ptr;
+__device__ inline coef_ptr coef(const double *table) {
+  coef_ptr p = (coef_ptr)table;
+  asm volatile("" : "+s"(p));  // a uniform address the compiler does not look through
+  return p;
+}
+#else
+typedef const double *coef_ptr;
+inline coef_ptr coef(const double *table) { return table; }
+#endif
+
+template <int N>
+__host__ __device__ inline void debye_n(int l, double x, double ix, double (&out)[N]) {
+  double f[N], yp[N], q[N], z[N], y[N], S[N], g[N];
+  coef_ptr ce = coef(kEtaC);
+#pragma unroll
+  for (int v = 0; v < N; ++v) {
+    const double nu = (double)(l + v) + 0.5;
+    const double d = nu - x, ie = 1.0 / (nu + x);
+    q[v] = sqrt(d * (nu + x));
+    yp[v] = d * ie;
+    g[v] = 2.0 * nu * (q[v] * ie);
+    f[v] = ce[kEtaDeg];
   }
+#pragma unroll
+  for (int m = kEtaDeg - 1; m >= 0; --m)
+#pragma unroll
+    for (int v = 0; v < N; ++v) f[v] = fma(f[v], yp[v], ce[m]);
   // u_k(t) / nu^k = z^k P_k(t^2) with t = nu / q, z = t / nu = 1 / q
-  const double z = 1.0 / q, t = nu * z, y = t * t;
-  double S = 0.0;
-#pragma unroll 1
-  for (int k = kDebyeK; k >= 1; --k) {
-    const double *c = kDebyeC + kDebyeOff[k];
-    double p = c[k];
-#pragma unroll 1
-    for (int i = k - 1; i >= 0; --i) p = fma(p, y, c[i]);
-    S = (S + p) * z;
+#pragma unroll
+  for (int v = 0; v < N; ++v) {
+    const double nu = (double)(l + v) + 0.5;
+    f[v] = exp(-yp[v] * fma(g[v], f[v], q[v]));  // e^eta
+    z[v] = 1.0 / q[v];
+    const double t = nu * z[v];
+    y[v] = t * t;
+    S[v] = 0.0;
   }
-  return exp(eta) * (1.0 + S) / (2.0 * sqrt(x * q));
+#pragma unroll
+  for (int k = kDebyeK; k >= 1; --k) {
+    coef_ptr c = coef(kDebyeC + kDebyeOff[k]);
+    double p[N];
+#pragma unroll
+    for (int v = 0; v < N; ++v) p[v] = c[k];
+#pragma unroll
+    for (int i = k - 1; i >= 0; --i)
+#pragma unroll
+      for (int v = 0; v < N; ++v) p[v] = fma(p[v], y[v], c[i]);
+#pragma unroll
+    for (int v = 0; v < N; ++v) S[v] = (S[v] + p[v]) * z[v];
+  }
+  // 1 / (2 sqrt(x q)) = z sqrt(q / x) / 2
+#pragma unroll
+  for (int v = 0; v < N; ++v) out[v] = f[v] * (1.0 + S[v]) * (0.5 * z[v] * sqrt(q[v] * ix));
+}
+
+__host__ __device__ inline double debye_j(int l, double x) {
+  double j[1];
+  debye_n<1>(l, x, 1.0 / x, j);
+  return j[0];
 }
 
 // One step of the three-term recurrence with coefficient t = (2l+1)/x:
@@ -193,10 +237,11 @@ __host__ __device__ inline int node_top_pair(double x, double ix, double wt, int
     if (Rc < lmin) return -1;
     const int R = lmin + (Rc - lmin) / 16 * 16 + 15;
     const int Ld = max(L0, R);
-    double hc = debye_j(Ld, x), hn = debye_j(Ld + 1, x);
-    run_down(hn, hc, Ld, R, ix);
-    cur = wt * hc;
-    nxt = wt * hn;
+    double h[2];  // j_Ld, j_{Ld+1}
+    debye_n<2>(Ld, x, ix, h);
+    run_down(h[1], h[0], Ld, R, ix);
+    cur = wt * h[0];
+    nxt = wt * h[1];
     return R;
   }
   const double s = sin(x), c = cos(x);
