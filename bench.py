@@ -65,7 +65,7 @@ def fp64_kernel():
     """(kernel name, source file) of the FP64 projection los_project launches."""
     if os.environ.get("LOS_PROJ_SCHEME", "1").strip() == "0":
         return "project_fp64_kernel", "project_fp64.hip"
-    return "project_fp64_desc_kernel", "project_fp64_desc_kernel.hpp"
+    return "project_fp64_sweep_kernel", "project_fp64_sweep_kernel.hpp"
 
 
 def traffic_for(prec, wl):

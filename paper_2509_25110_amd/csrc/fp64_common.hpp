@@ -1,5 +1,5 @@
-// Device helpers shared by the FP64 projection kernels (project_fp64.hip,
-// project_fp64_desc.hip): the per-block sum over tau of a workgroup's lanes
+// Device helpers of the FP64 projection kernels (project_fp64.hip,
+// project_fp64_sweep_kernel.hpp): the per-block sum over tau of a workgroup's lanes
 // (fixed order, bitwise reproducible), source loads and wave-uniform slot tests.
 #pragma once
 

@@ -370,18 +370,18 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
   const bool desc = !(scheme && std::atoi(scheme) == 0);
   if (!desc && kernel_mask != 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project: the E-mode kernel needs the sweep scheme");
-  los::ProjectShape sh =
-      desc ? los::project_fp64_desc_shape(nsrc, ntau, env_int("LOS_PROJ_WAVES"),
-                                          env_int("LOS_PROJ_SLOTS"),
-                                          kernel_mask ? 16 : env_int("LOS_PROJ_BLOCK"),
-                                          (size_t)std::max(0, env_int("LOS_PROJ_LDS_EXTRA")))
-           : los::project_fp64_shape(nsrc, ntau, env_int("LOS_PROJ_WAVES"),
-                                     env_int("LOS_PROJ_SLOTS"));
-  if (sh.waves == 0)
-    return fail(LOS_ERR_UNSUPPORTED, "los_project: no launch shape for ntau = %lld",
-                (long long)ntau);
-  if (sh.lds > 160 * 1024)
-    return fail(LOS_ERR_UNSUPPORTED, "los_project: needs %zu bytes of LDS", sh.lds);
+  los::SweepShape sw{};
+  los::ProjectShape sh{};
+  if (desc) {
+    sw = los::project_sweep_shape(nsrc, nk, ntau, env_int("LOS_PROJ_WAVES"));
+  } else {
+    sh = los::project_fp64_shape(nsrc, ntau, env_int("LOS_PROJ_WAVES"), env_int("LOS_PROJ_SLOTS"));
+    if (sh.waves == 0)
+      return fail(LOS_ERR_UNSUPPORTED, "los_project: no launch shape for ntau = %lld",
+                  (long long)ntau);
+    if (sh.lds > 160 * 1024)
+      return fail(LOS_ERR_UNSUPPORTED, "los_project: needs %zu bytes of LDS", sh.lds);
+  }
   los::ProjectArgs a{};
   a.lmin = lmin;
   a.lmax = lmax;
@@ -396,7 +396,7 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
   a.S = (const double *)S;
   a.delta = (double *)delta;
   a.emask = kernel_mask;
-  hipError_t e = desc ? los::project_fp64_desc_launch(a, nsrc, sh, (hipStream_t)stream)
+  hipError_t e = desc ? los::project_sweep_launch(a, nsrc, sw, false, (hipStream_t)stream)
                       : los::project_fp64_launch(a, nsrc, sh, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "los_project launch");
   const int rc = los::check_result("los_project", delta, nk * (int64_t)a.nl * nsrc, false,
@@ -430,12 +430,7 @@ int los_project_tensor(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, int
   if (scheme && std::atoi(scheme) == 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project_tensor: needs the sweep scheme");
   // the sweep: rows lmin-1 .. lmax, columns S_P, S_P/x, S_P/x^2, S_T/x^2
-  los::ProjectShape sh = los::project_fp64_desc_shape(
-      4, ntau, env_int("LOS_PROJ_WAVES"), env_int("LOS_PROJ_SLOTS"), 16,
-      (size_t)std::max(0, env_int("LOS_PROJ_LDS_EXTRA")));
-  if (sh.waves == 0 || sh.lds > 160 * 1024)
-    return fail(LOS_ERR_UNSUPPORTED, "los_project_tensor: no launch shape for ntau = %lld",
-                (long long)ntau);
+  const los::SweepShape sh = los::project_sweep_shape(4, nk, ntau, env_int("LOS_PROJ_WAVES"));
   const int nl = lmax - lmin + 1;
   void *ws = nullptr;
   int rc = ws_reserve(ctx, WS_TENSOR, sizeof(double) * 4 * (size_t)(nl + 1) * (size_t)nk, &ws);
@@ -461,7 +456,7 @@ int los_project_tensor(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, int
   a.splane[2] = 1;
   a.splane[3] = 0;
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = los::project_fp64_desc_launch(a, 4, sh, st);
+  hipError_t e = los::project_sweep_launch(a, 4, sh, false, st);
   if (e != hipSuccess) return hip_fail(e, "los_project_tensor: sweep launch");
   e = los::tensor_combine_launch((const double *)ws, delta, lmin, nl, nk, st);
   if (e != hipSuccess) return hip_fail(e, "los_project_tensor: combine launch");
@@ -500,12 +495,7 @@ int los_project_lsample(los_ctx *ctx, int32_t lmin, int32_t lmax, const int32_t 
   const char *scheme = std::getenv("LOS_PROJ_SCHEME");
   if (scheme && std::atoi(scheme) == 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project_lsample: needs the sweep scheme");
-  los::ProjectShape sh = los::project_fp64_desc_shape(
-      nsrc, ntau, env_int("LOS_PROJ_WAVES"), env_int("LOS_PROJ_SLOTS"), 16,
-      (size_t)std::max(0, env_int("LOS_PROJ_LDS_EXTRA")));
-  if (sh.waves == 0 || sh.lds > 160 * 1024)
-    return fail(LOS_ERR_UNSUPPORTED, "los_project_lsample: no launch shape for ntau = %lld",
-                (long long)ntau);
+  const los::SweepShape sh = los::project_sweep_shape(nsrc, nk, ntau, env_int("LOS_PROJ_WAVES"));
   // device tables (output row per multipole, sampled-row mask per 16-row
   // block), rebuilt only when the list changes
   const int nl = lmax - lmin + 1, nblk = (nl + 15) / 16;
@@ -555,7 +545,7 @@ int los_project_lsample(los_ctx *ctx, int32_t lmin, int32_t lmax, const int32_t 
   a.lsel = (const int32_t *)ws;
   a.bmask = (const uint32_t *)((const char *)ws + sizeof(int32_t) * (size_t)nl);
   a.nls = nls;
-  hipError_t e = los::project_fp64_desc_launch(a, nsrc, sh, st);
+  hipError_t e = los::project_sweep_launch(a, nsrc, sh, false, st);
   if (e != hipSuccess) return hip_fail(e, "los_project_lsample launch");
   const int rc2 = los::check_result("los_project_lsample", delta, nk * (int64_t)nls * nsrc, false, st);
   return rc2 == LOS_OK ? ok() : rc2;

@@ -34,32 +34,37 @@ struct ProjectArgs {
   const int32_t *lsel = nullptr;
   const uint32_t *bmask = nullptr;
   int nls = 0;
-  // sweep kernel: blocks of partial sums kept in LDS (2 or 8; the workgroup
-  // synchronises every ring/2 blocks).  Set from ProjectShape::ring.
-  int ring = 8;
+  // Sweep kernel: this launch's tau nodes n0 .. n0 + ncnt - 1 (set per pass by the
+  // launcher); accumulate: add to the delta of the passes before.
+  int n0 = 0, ncnt = 0;
+  bool accumulate = false;
 };
 
-// Launch shape chosen by the host for the FP64 projection.
+// Launch shape of the two-pass FP64 projection.
 struct ProjectShape {
-  int waves;      // waves per workgroup (1..8)
-  int slots;      // tau slots per lane (4, 8, 12, 16)
-  size_t lds;     // dynamic LDS bytes
-  int block = 8;  // l rows per block (descending sweep: 8 or 16)
-  int ring = 8;   // descending sweep: blocks of partials in LDS (2 or 8)
+  int waves;   // waves per workgroup (1..8)
+  int slots;   // tau slots per lane
+  size_t lds;  // dynamic LDS bytes
 };
 
-// FP64 projection: one workgroup per k.
+// Two-pass FP64 projection: one workgroup per k.
 // force_waves / force_slots > 0 override the default shape (tuning).
 ProjectShape project_fp64_shape(int nsrc, int64_t ntau, int force_waves = 0, int force_slots = 0);
 hipError_t project_fp64_launch(const ProjectArgs &a, int nsrc, const ProjectShape &sh,
                                hipStream_t s);
-// Single descending sweep variant (project_fp64_desc.hip), same arguments.
-// block: 8 or 16 (default, also for 0) rows per reduction; lds_extra:
-// additional LDS per workgroup (bounds the workgroups per CU).
-ProjectShape project_fp64_desc_shape(int nsrc, int64_t ntau, int force_waves = 0,
-                                     int force_slots = 0, int block = 8, size_t lds_extra = 0);
-hipError_t project_fp64_desc_launch(const ProjectArgs &a, int nsrc, const ProjectShape &sh,
-                                    hipStream_t s);
+
+// FP64 sweep (project_fp64_sweep*.hip): one workgroup of `waves` waves per k row,
+// rows in blocks of kSweepBlock, the tau nodes in passes of `nodes`.
+constexpr int kSweepBlock = 16;
+struct SweepShape {
+  int waves;
+  int nodes;   // nodes per pass (a multiple of 64, at most 8192)
+  size_t lds;  // dynamic LDS bytes
+};
+SweepShape project_sweep_shape(int nsrc, int64_t nk, int64_t ntau, int force_waves = 0);
+// f32: S and delta are float (plain columns only); every sum is FP64 all the same.
+hipError_t project_sweep_launch(const ProjectArgs &a, int nsrc, const SweepShape &sh, bool f32,
+                                hipStream_t s);
 
 // Weighted Bessel tables for the MFMA projection (see jtable.hip):
 // J[(kc*nlp + l - lmin)*ntp + n] = w_n j_l(k[k0 + kc] (tau0 - tau_n)) in FP32,

@@ -1,0 +1,86 @@
+// FP64 sweep: launch shape and dispatch over the source count.  The kernel and its
+// description are in project_fp64_sweep_kernel.hpp; project_fp64_sweep_n{1..4}.hip
+// instantiate it.
+#include <algorithm>
+
+#include "project_fp64_sweep_kernel.hpp"
+
+namespace los {
+
+hipError_t project_sweep_launch_n1(const ProjectArgs &a, const SweepShape &sh, bool f32, bool scaled,
+                                   hipStream_t s);
+hipError_t project_sweep_launch_n2(const ProjectArgs &a, const SweepShape &sh, bool f32, bool scaled,
+                                   hipStream_t s);
+hipError_t project_sweep_launch_n3(const ProjectArgs &a, const SweepShape &sh, bool f32, bool scaled,
+                                   hipStream_t s);
+hipError_t project_sweep_launch_n4(const ProjectArgs &a, const SweepShape &sh, bool f32, bool scaled,
+                                   hipStream_t s);
+
+namespace {
+
+// LDS of a workgroup: per node the pair, 1/x and the block of R; per wave the reduction
+// stage and the progress word; two thresholds per slot.
+size_t sweep_lds(int W, int64_t nodes, int nsrc) {
+  return (size_t)nodes * (2 * sizeof(double) + sizeof(double) + sizeof(short)) +
+         (size_t)W * (sizeof(double) * sweep::stage_doubles(nsrc) + sizeof(int)) +
+         2 * sizeof(short) * (size_t)(nodes / 64);
+}
+
+}  // namespace
+
+// Waves per workgroup.  More waves share a row's blocks, more workgroups on a CU work on
+// rows that do not wait for each other.  Measured over W = 2 .. 16 on 20 shapes (1 to 4
+// columns, 165 to 3052 nodes, 66 to 2115 rows), a multiple of 4 (every SIMD has the same
+// number) is always within 4 % of the best, and the best is the largest
+//   W g / (1 + W / 10),  g = workgroups on a CU: what LDS and registers allow, at most nk / 256
+// e.g. 1751 nodes, 4 columns, 1253 rows: 4 waves 246 us (two workgroups), 8 waves 291 us (one);
+// 565 nodes, 4 columns, 382 rows: 190 and 141 us; C2 (3000 nodes, one workgroup by LDS): 4,
+// 8, 12 waves 2.89, 2.10, 1.92 ms; 1777 nodes, 2 columns, 1501 rows: 4, 8, 12 waves 294,
+// 245, 280 us.
+SweepShape project_sweep_shape(int nsrc, int64_t nk, int64_t ntau, int force_waves) {
+  constexpr size_t kLds = 160 * 1024;
+  const int wmax = sweep::max_waves(nsrc);
+  // nodes per pass: all of them if 4 waves fit beside their LDS, else equal shares
+  int64_t nodes = 0;
+  for (int64_t passes = 1;; ++passes) {
+    nodes = ((ntau + passes - 1) / passes + 63) / 64 * 64;
+    if (nodes <= 64 * 128 && sweep_lds(4, nodes, nsrc) <= kLds) break;
+  }
+  int W = force_waves < wmax ? force_waves : wmax;
+  if (force_waves <= 0) {
+    double best = 0.0;
+    for (int w = 4; w <= wmax; w += 4) {
+      const size_t lds = sweep_lds(w, nodes, nsrc);
+      if (lds > kLds) break;
+      double g = (double)std::min<size_t>(kLds / lds, (size_t)(wmax / w));
+      g = std::min(g, (double)nk / 256.0);
+      const double score = w * g / (1.0 + 0.1 * w);
+      if (score > best) {
+        best = score;
+        W = w;
+      }
+    }
+  }
+  while (sweep_lds(W, nodes, nsrc) > kLds) --W;
+  SweepShape sh{};
+  sh.waves = W;
+  sh.nodes = (int)nodes;
+  sh.lds = sweep_lds(W, nodes, nsrc);
+  return sh;
+}
+
+hipError_t project_sweep_launch(const ProjectArgs &a, int nsrc, const SweepShape &sh, bool f32,
+                                hipStream_t s) {
+  // scaled columns or remapped source planes take the scaled variants
+  bool sc = (a.emask | a.x1mask | a.x2mask) != 0u;
+  for (int q = 0; q < nsrc && q < 4; ++q) sc = sc || a.splane[q] != q;
+  switch (nsrc) {
+    case 1: return project_sweep_launch_n1(a, sh, f32, sc, s);
+    case 2: return project_sweep_launch_n2(a, sh, f32, sc, s);
+    case 3: return project_sweep_launch_n3(a, sh, f32, sc, s);
+    case 4: return project_sweep_launch_n4(a, sh, f32, sc, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace los

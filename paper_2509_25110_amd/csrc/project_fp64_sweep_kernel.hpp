@@ -1,0 +1,363 @@
+// FP64 line-of-sight projection, one descending sweep per k row (gCAMB paper
+// Sec. 2.1 Eq. 2-3; Sec. 3.2 / Algorithm 1 for the k / l / tau loops):
+//
+//   delta[k][l][s] = sum_n w_n S[s][k][n] j_l(k (tau0 - tau_n))
+//
+// One workgroup of W waves per k row, the largest k first.  The tau nodes go in
+// slots of 64 (one node per lane), the multipoles in blocks of 16 rows counted
+// from lmin.
+//   * setup (all waves, slots dealt out): each node finds the pair w (j_R, j_{R+1})
+//     at its top row R, the top row of the block that holds min(ltop(x), lmax).
+//     For x >= lmax + 1 the upward recurrence from j_{-1} = cos x / x, j_0 =
+//     sin x / x runs to R + 1 (stable on the oscillatory side; R is at most 15 rows
+//     past lmax, and those rows are never stored).  Otherwise, for x >= kXDebye,
+//     Debye's expansion gives the pair at Ls = max(ltop(x), R) and the recurrence
+//     runs down to R; for smaller x the upward run goes to m = floor(x) for j_m, and
+//     Miller's recurrence with seeds (0, 1) from Ls runs down to m and is scaled there
+//     to j_m (j_m is near the last maximum in l, never near a zero).  The pair, 1/x and
+//     the block of R go to LDS.
+//   * sweep: wave w takes the blocks first - w, first - w - W, ... and walks all
+//     slots that are live in its block, so the sums of a block over every node stay in
+//     one wave's registers (16 x NSRC accumulators per lane).  For a slot it reads the
+//     nodes' pairs from LDS, runs j_{l-1} = (2l+1)/x j_l - j_{l+1} down the 16 rows
+//     (downward is stable above the turning point and neutral below it) and writes the
+//     pairs back for the wave that owns the next lower block.  That wave follows one
+//     slot or more behind: each wave publishes how far it is in LDS (prog), and waits
+//     only when it has caught up with the wave above.
+//   * a block's sums are reduced over the lanes once, by its wave, and stored.
+// Why this split: the sweep is bound by FP64 VALU issue.  With the nodes of a row
+// divided among the waves instead (each wave walking every block, the pairs in
+// registers), every wave reduces every block over its lanes, which was 30 % of the
+// VALU instructions, the unrolled slots take 220 registers (2 waves per SIMD), each
+// block re-reads the row's sources from L2, and a short row keeps one wave busy for
+// its whole length.  Here a block is reduced once, W blocks in flight share each
+// slot's sources through the L1 cache, and a row of few slots still spreads over W
+// waves.
+//
+// E-mode sources (bit s of emask; Sec. 2.1, Eq. 3: eps_l(x) =
+// sqrt((l+2)!/(l-2)!) j_l(x) / x^2): their values are scaled by 1/x^2 per node
+// as they are used and their output rows by sqrt((l-1) l (l+1) (l+2)); a node
+// with x below kXTiny adds its limit w S sqrt(24)/15 to l = 2 only.
+// Columns of x1mask / x2mask are scaled by 1/x / 1/x^2 per node with no row
+// factor (the tensor-mode projection combines them afterwards); their x -> 0
+// limits go to l = 1 (w S / 3) and l = 2 (w S / 15).  Column s reads source
+// plane splane[s], so one source can feed several columns.
+#pragma once
+
+#include "bessel_dev.hpp"
+#include "fp64_common.hpp"
+#include "los_internal.hpp"
+
+namespace los {
+namespace sweep {
+
+using fp64::wave_max;
+using fp64::wave_min;
+
+constexpr int B = kSweepBlock;
+
+// Most waves of a workgroup: their registers bound the waves a SIMD can hold.
+constexpr int max_waves(int nsrc) { return nsrc <= 2 ? 16 : nsrc == 3 ? 12 : 8; }
+
+// One slot over the block of rows top .. top-15, descending.  (p1, p0) =
+// (w j_{l+1}, w j_l) at l = top on entry, at l = top - 16 on return.
+template <int NSRC>
+__device__ __forceinline__ void sweep_slot(double (&acc)[B * NSRC], double &p1, double &p0,
+                                           double ix, const double (&sv)[NSRC], int top) {
+  double t = 0.0;
+  const double d2 = ix + ix;
+#pragma unroll
+  for (int i = 0; i < B; ++i) {
+    // the coefficient (2l+1)/x is formed exactly every 8 rows and stepped by
+    // -2/x in between (at most 7 rounding steps)
+    if (i % 8 == 0) t = (double)(2 * (top - i) + 1) * ix;
+    const int q = (B - 1 - i) * NSRC;
+#pragma unroll
+    for (int s = 0; s < NSRC; ++s) acc[q + s] = fma(p0, sv[s], acc[q + s]);
+    const double nx = rec_step(t, p0, p1);
+    p1 = p0;
+    p0 = nx;
+    t -= d2;
+  }
+}
+
+// Orders a wave's LDS accesses and keeps its lanes together: a wave's LDS operations are
+// performed in order, so no wait is needed, but the compiler must neither move accesses
+// across this point nor let one side of a divergent branch run ahead of it.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// A block's NV = 16 NSRC sums over a wave's lanes.  Two exchange steps (lanes 32 and 16
+// apart) leave NV / 4 values per lane, summed over 4 lanes; these go through the wave's LDS
+// stage, [16][NV / H + 1] (the pad keeps both its accesses free of bank conflicts), in H
+// rounds.  f(e, total) is called by the lane that holds the total of value e.  Two rounds
+// (from 2 columns on) halve the stage, which decides how many waves fit a CU's LDS.
+constexpr int reduce_rounds(int nsrc) { return nsrc == 1 ? 1 : 2; }
+constexpr int stage_doubles(int nsrc) { return 16 * (B * nsrc / reduce_rounds(nsrc) + 1); }
+
+template <int NSRC, typename F>
+__device__ __forceinline__ void reduce_block(double (&v)[B * NSRC], double *stage, int lane, F f) {
+  constexpr int NV = B * NSRC, H = reduce_rounds(NSRC), P = NV / 4 / H, LD = NV / H + 1;
+  double u[NV / 2], q[NV / 4];
+#pragma unroll
+  for (int p = 0; p < NV / 2; ++p) u[p] = fp64::swap_add32(v[p], v[p + NV / 2]);
+#pragma unroll
+  for (int p = 0; p < NV / 4; ++p) q[p] = fp64::swap_add16(u[p], u[p + NV / 4]);
+  // lane (r, c) now holds, for value p + r NV / 4, the sum over the 4 lanes of column c
+  const int r = lane >> 4, c = lane & 15;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) stage[c * LD + r * P + p] = q[h * P + p];
+    wave_sync();
+    if (lane < 4 * P) {
+      double tot = 0.0;
+#pragma unroll
+      for (int cc = 0; cc < 16; ++cc) tot += stage[cc * LD + lane];
+      f(lane / P * (NV / 4) + h * P + lane % P, tot);
+    }
+    wave_sync();
+  }
+}
+
+// The members of a set of up to 128 slots in increasing order (uniform).
+struct SlotList {
+  uint64_t a, b;
+  __device__ int pop() {  // the next one, or -1
+    if (a) {
+      const int s = __builtin_ctzll(a);
+      a &= a - 1;
+      return s;
+    }
+    if (b) {
+      const int s = 64 + __builtin_ctzll(b);
+      b &= b - 1;
+      return s;
+    }
+    return -1;
+  }
+};
+
+// T: type of the sources and of delta (float: the sources are widened as they are
+// used, every sum is FP64, and delta is rounded once).  SMP: multipole sampling.
+// SC: the variant with per-column scalings (E-mode, 1/x, 1/x^2) and source planes;
+// without it every column s reads plane s unscaled.
+template <typename T, int NSRC, bool SMP, bool SC>
+__global__ void __launch_bounds__(64 * max_waves(NSRC)) project_fp64_sweep_kernel(ProjectArgs a) {
+  constexpr int NV = B * NSRC;
+  extern __shared__ __attribute__((aligned(16))) double lds[];
+
+  const int W = blockDim.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t ki = a.nk - 1 - (int64_t)blockIdx.x;  // large k (most work) first
+  const int lmin = a.lmin, lmax = a.lmax;
+  const int nblk = (a.nl + B - 1) / B;
+  const int n0 = a.n0, ncnt = a.ncnt;  // this pass's nodes
+  const int nslot = (ncnt + 63) >> 6, npad = nslot << 6;
+
+  double *ixs = lds;                                // [npad] 1/x
+  double2 *st = (double2 *)(ixs + npad);            // [npad] (w j_l, w j_{l+1}) at the next row
+  double *stages = ixs + 3 * npad, *stage = stages + w * stage_doubles(NSRC);  // per wave
+  short *rb = (short *)(stages + W * stage_doubles(NSRC));  // [npad] block of R
+  short *thA = rb + npad, *thF = thA + nslot;       // per slot: live / fully live up to this block
+  int *prog = (int *)(thF + nslot);                 // [W] progress of each wave
+
+  const double kk = a.k[ki];
+  const T *srow[NSRC];
+#pragma unroll
+  for (int s = 0; s < NSRC; ++s)
+    srow[s] = (const T *)a.S + ((int64_t)(SC ? a.splane[s] : s) * a.nk + ki) * a.ntau + n0;
+
+  // ---------------- per-node setup: the pair at the top row ----------------
+  // Every node's top row R is the top row of a block, so in any block a lane is
+  // either live throughout or not at all.  Rows between the band edge and R hold
+  // values below the band cut; rows above lmax are swept but never stored.
+  const int top_all = lmin + (lmax - lmin) / B * B + (B - 1);
+  const bool lim1 = SC && a.x1mask != 0 && lmin <= 1;
+  const bool lim2 = SC && (a.emask | a.x2mask) != 0 && lmin <= 2;
+  constexpr int kTinyNode = -2;  // rb of a node below kXTiny with a limit term
+  for (int s = w; s < nslot; s += W) {
+    const int i = s * 64 + lane;
+    const int n = n0 + (i < ncnt ? i : ncnt - 1);
+    const double x = kk * (a.tau0 - a.tau[n]), wn = a.w[n];
+    const bool live = i < ncnt && x >= kXTiny && wn != 0.0;
+    const bool tiny = i < ncnt && (lim1 || lim2) && x < kXTiny;
+    const double ix = live ? 1.0 / x : 0.0;
+    const int m = live ? (int)floor(x) : 0;
+    const bool osc = m >= lmax + 1;  // every row up to R is on the oscillatory side
+    int R = -1;
+    double cur = 0.0, nxt = 0.0;
+    if (live) {
+      const int L0 = ltop_of(x);
+      const int Rc = osc || L0 > lmax ? lmax : L0;  // last row kept (band edge or lmax)
+      if (Rc >= lmin) {
+        // top row of the block holding Rc; Debye's and Miller's seeds sit at or above it
+        R = lmin + (Rc - lmin) / B * B + (B - 1);
+        const int Ls = L0 > R ? L0 : R;
+        if (!osc && x >= kXDebye) {
+          double h[2];  // j_Ls, j_{Ls+1}
+          debye_n<2>(Ls, x, ix, h);
+          run_down(h[1], h[0], Ls, R, ix);
+          cur = wn * h[0];
+          nxt = wn * h[1];
+        } else {
+          double sn, cs;
+          sincos(x, &sn, &cs);
+          cur = wn * (cs * ix);  // w j_{-1}
+          nxt = wn * (sn * ix);  // w j_0
+          run_up(cur, nxt, 0, osc ? R + 1 : m, ix);
+          if (!osc) {
+            double hn = 0.0, hc = 1.0;  // Miller seeds (0, 1) at Ls
+            run_down(hn, hc, Ls, R, ix);
+            const double hR = hc, hR1 = hn;
+            run_down(hn, hc, R, m, ix);
+            const double sc = nxt / hc;  // w j_m / its Miller value
+            cur = sc * hR;
+            nxt = sc * hR1;
+          }
+        }
+      }
+    }
+    const int b = R >= lmin ? (R - lmin) / B : -1;
+    const int bmax = wave_max(b), bmin = wave_min(b);
+    st[i] = make_double2(cur, nxt);
+    ixs[i] = ix;
+    rb[i] = (short)(tiny ? kTinyNode : b);
+    if (lane == 0) {
+      thA[s] = (short)bmax;
+      thF[s] = (short)bmin;
+    }
+  }
+  if (lane == 0) prog[w] = 0;
+  __syncthreads();
+
+  // Slot thresholds, lane j holding slots j and 64 + j; the highest live block.
+  const int tA0 = lane < nslot ? thA[lane] : -1, tA1 = lane + 64 < nslot ? thA[lane + 64] : -1;
+  const int tF0 = lane < nslot ? thF[lane] : -1, tF1 = lane + 64 < nslot ? thF[lane + 64] : -1;
+  int first = wave_max(tA0 > tA1 ? tA0 : tA1);
+
+  T *drow = (T *)a.delta + ki * (int64_t)(SMP ? a.nls : a.nl) * NSRC;
+  // output offset of row l = b + e / NSRC, source e % NSRC (-1: not stored)
+  auto out_at = [&](int b, int e) -> int64_t {
+    const int l = b + e / NSRC;
+    if (l > lmax) return -1;
+    if (!SMP) return (int64_t)(b - lmin) * NSRC + e;
+    const int r = a.lsel[l - lmin];
+    return r < 0 ? -1 : (int64_t)r * NSRC + e % NSRC;
+  };
+  // with limit terms, block 0 is summed even when no node reaches it
+  if ((lim1 || lim2) && first < 0) first = 0;
+  if (!a.accumulate) {  // blocks above every node's top row are zero
+    for (int e = (first + 1) * NV + (int)threadIdx.x; e < nblk * NV; e += blockDim.x) {
+      const int64_t o = out_at(lmin + e / NV * B, e % NV);
+      if (o >= 0) drow[o] = (T)0;
+    }
+  }
+
+  // ---------------- sweep ----------------
+  const int pred = w > 0 ? w - 1 : W - 1;  // the wave that owns the block above
+  int known = 0;                           // how far it is known to be
+  int it = 0;
+  const unsigned last = (unsigned)(ncnt - 1) * (unsigned)sizeof(T);
+  for (int bi = first - w; bi >= 0; bi -= W, ++it) {
+    const int b = lmin + bi * B, top = b + B - 1;
+    SlotList live{__ballot(tA0 >= bi), __ballot(tA1 >= bi)};
+    const uint64_t fullA = __ballot(tF0 >= bi), fullB = __ballot(tF1 >= bi);  // every lane live
+    // progress the wave above must have reached for slot s: 128 a block, s + 1 within it;
+    // the top block waits for nobody
+    const int base = w > 0 ? it * 128 : (it - 1) * 128;
+    const uint32_t rows = SMP ? a.bmask[bi] : 0xffffu;  // sampled rows (bit r: row b + r)
+    double acc[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) acc[q] = 0.0;
+    auto load = [&](T (&sv)[NSRC], int s) {
+      unsigned off = (unsigned)(s * 64 + lane) * (unsigned)sizeof(T);
+      off = off < last ? off : last;  // lanes past the end read the last node (not used)
+#pragma unroll
+      for (int q = 0; q < NSRC; ++q) sv[q] = *(const T *)((const char *)srow[q] + off);
+    };
+    auto step = [&](int s, const T (&raw)[NSRC], int snext) {
+      if (w > 0 || it > 0) {
+        const int need = base + s + 1;
+        while (known < need) {
+          known = __builtin_amdgcn_readfirstlane(
+              __hip_atomic_load(&prog[pred], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+          if (known < need) __builtin_amdgcn_s_sleep(1);
+        }
+        wave_sync();
+      }
+      const int i = s * 64 + lane;
+      if ((((s < 64 ? fullA : fullB) >> (s & 63)) & 1u) || rb[i] >= bi) {  // the node is live
+        const double2 pr = st[i];
+        const double ix = ixs[i];
+        double p0 = pr.x, p1 = pr.y;
+        double sv[NSRC];
+#pragma unroll
+        for (int q = 0; q < NSRC; ++q) sv[q] = (double)raw[q];
+        if (SC) {
+          const double i2 = ix * ix;
+#pragma unroll
+          for (int q = 0; q < NSRC; ++q) {
+            if (((a.emask | a.x2mask) >> q) & 1u) sv[q] *= i2;
+            else if ((a.x1mask >> q) & 1u) sv[q] *= ix;
+          }
+        }
+        sweep_slot<NSRC>(acc, p1, p0, ix, sv, top);
+        st[i] = make_double2(p0, p1);
+      }
+      // the pairs are in place before the progress that announces them: every slot below
+      // the next live one is done
+      wave_sync();
+      __hip_atomic_store(&prog[w], snext >= 0 ? it * 128 + snext : (it + 1) * 128,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // the next slot's sources are loaded while this one is swept
+    T sa[NSRC], sb[NSRC];
+    int s = live.pop();
+    if (s >= 0) load(sa, s);
+    while (s >= 0) {
+      const int s2 = live.pop();
+      if (s2 >= 0) load(sb, s2);
+      step(s, sa, s2);
+      if (s2 < 0) break;
+      s = live.pop();
+      if (s >= 0) load(sa, s);
+      step(s2, sb, s);
+    }
+    if (SC && bi == 0 && (lim1 || lim2)) {
+      // Limits at x -> 0 of the scaled columns (the nodes below kXTiny are not swept):
+      // j_2(x)/x^2 -> 1/15 for E-mode and 1/x^2 columns at l = 2, j_1(x)/x -> 1/3 for
+      // 1/x columns at l = 1; every other row -> 0.
+      const uint32_t m2 = a.emask | a.x2mask, m1 = a.x1mask;
+      for (int sl = 0; sl < nslot; ++sl) {
+        const int n = sl * 64 + lane;
+        if (rb[n] != kTinyNode) continue;
+        const double wn = a.w[n0 + n];
+#pragma unroll
+        for (int q = 0; q < NSRC; ++q) {
+          const double e2 = lim2 && ((m2 >> q) & 1u) ? wn * (double)srow[q][n] * (1.0 / 15.0) : 0.0;
+          const double e1 = lim1 && ((m1 >> q) & 1u) ? wn * (double)srow[q][n] * (1.0 / 3.0) : 0.0;
+          if (lmin == 1) {
+            acc[q] += e1;         // row 1
+            acc[NSRC + q] += e2;  // row 2
+          } else {                // lmin == 2
+            acc[q] += e2;
+          }
+        }
+      }
+    }
+    if (rows == 0u) continue;  // no sampled row in this block (uniform)
+    reduce_block<NSRC>(acc, stage, lane, [&](int e, double tot) {
+      const int l = b + e / NSRC;
+      if (SC && ((a.emask >> (e % NSRC)) & 1u))
+        tot *= sqrt((double)(l - 1) * (double)l * (double)(l + 1) * (double)(l + 2));
+      const int64_t o = out_at(b, e);
+      if (o >= 0) drow[o] = (T)(a.accumulate ? tot + (double)drow[o] : tot);
+    });
+  }
+}
+
+}  // namespace sweep
+}  // namespace los

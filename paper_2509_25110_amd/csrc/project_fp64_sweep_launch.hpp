@@ -1,0 +1,47 @@
+// Launches of the FP64 sweep for one source count.
+#pragma once
+
+#include "project_fp64_sweep_kernel.hpp"
+
+namespace los {
+namespace sweep {
+
+template <typename T, int NSRC, bool SMP, bool SC>
+hipError_t launch_t(const ProjectArgs &a, const SweepShape &sh, hipStream_t s) {
+  auto kern = project_fp64_sweep_kernel<T, NSRC, SMP, SC>;
+  if (sh.waves < 1 || sh.waves > max_waves(NSRC) || sh.nodes < 64 || sh.nodes > 64 * 128)
+    return hipErrorInvalidValue;
+  if (sh.lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void *)kern,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds);
+    if (e != hipSuccess) return e;
+  }
+  ProjectArgs b = a;
+  for (int64_t n0 = 0; n0 < a.ntau; n0 += sh.nodes) {
+    b.n0 = (int)n0;
+    b.ncnt = (int)(a.ntau - n0 < sh.nodes ? a.ntau - n0 : sh.nodes);
+    b.accumulate = n0 > 0;
+    hipLaunchKernelGGL(kern, dim3((unsigned)b.nk), dim3(64 * sh.waves), sh.lds, s, b);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <int NSRC>
+hipError_t launch(const ProjectArgs &a, const SweepShape &sh, bool f32, bool scaled,
+                  hipStream_t s) {
+  if (a.lsel && !a.bmask) return hipErrorInvalidValue;
+  if (f32) {
+    if (scaled || a.lsel) return hipErrorInvalidValue;
+    return launch_t<float, NSRC, false, false>(a, sh, s);
+  }
+  if (scaled)
+    return a.lsel ? launch_t<double, NSRC, true, true>(a, sh, s)
+                  : launch_t<double, NSRC, false, true>(a, sh, s);
+  return a.lsel ? launch_t<double, NSRC, true, false>(a, sh, s)
+                : launch_t<double, NSRC, false, false>(a, sh, s);
+}
+
+}  // namespace sweep
+}  // namespace los

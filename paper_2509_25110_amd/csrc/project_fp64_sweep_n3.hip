@@ -1,0 +1,12 @@
+// FP64 sweep (project_fp64_sweep_kernel.hpp) with 3 columns: the plain, sampled and scaled
+// variants on double sources and the plain one on float sources.
+#include "project_fp64_sweep_launch.hpp"
+
+namespace los {
+
+hipError_t project_sweep_launch_n3(const ProjectArgs &a, const SweepShape &sh, bool f32, bool scaled,
+                                   hipStream_t s) {
+  return sweep::launch<3>(a, sh, f32, scaled, s);
+}
+
+}  // namespace los
