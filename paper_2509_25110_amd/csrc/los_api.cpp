@@ -165,7 +165,7 @@ los::GemmTile gemm_tile_for(int max_ncol) {
   return {2, 4};
 }
 
-// Mixed-precision projection, default pipeline: per chunk of k rows the FP64
+// Mixed-precision projection on the matrix cores (LOS_MIXED_FUSED=1): per chunk of k rows the FP64
 // Bessel seeds (every 32 multipoles), then the product with the Bessel tiles
 // regenerated in LDS (project_fused.hip); no table reaches device memory.
 // The seed workspace is bounded by LOS_JTAB_MIB (default 4096 MiB);
@@ -347,10 +347,16 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
   if (nsrc < 32 && (kernel_mask >> nsrc) != 0)
     return fail(LOS_ERR_INVALID, "los_project: kernel mask 0x%x names a source >= nsrc = %d",
                 kernel_mask, nsrc);
-  if (prec != LOS_FP64) {
-    if (kernel_mask != 0)
-      return fail(LOS_ERR_UNSUPPORTED, "los_project: the E-mode kernel is FP64 only");
-    const char *fz = std::getenv("LOS_MIXED_FUSED");
+  // Mixed precision: float sources and delta.  A k row has at most 4 columns, of which the
+  // matrix cores use 16 at a time and for which they need every Bessel value generated, rounded
+  // and staged, so by default the FP64 sweep takes these too (widening the sources as it
+  // reads them): C3 in FP32 7.2 ms against 22.0 ms on the matrix cores, and no workspace.
+  // LOS_MIXED_FUSED or LOS_FUSED_SHAPE in the environment select the matrix-core pipelines.
+  const bool f32 = prec != LOS_FP64;
+  if (f32 && kernel_mask != 0)
+    return fail(LOS_ERR_UNSUPPORTED, "los_project: the E-mode kernel is FP64 only");
+  const char *fz = std::getenv("LOS_MIXED_FUSED");
+  if (f32 && (fz || std::getenv("LOS_FUSED_SHAPE"))) {
     const bool tables = fz && std::atoi(fz) == 0;
     int rc = tables ? project_mixed(ctx, lmin, lmax, nk, ntau, tau0, k, tau, w_tau,
                                     (const float *)S, nsrc, prec, (float *)delta,
@@ -364,10 +370,10 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
     return rc == LOS_OK ? ok() : rc;
   }
 
-  // Default: the single descending sweep; LOS_PROJ_SCHEME=0 selects the
+  // Default: the single descending sweep; LOS_PROJ_SCHEME=0 selects the FP64
   // two-pass kernel (ascending upward, then descending Miller).
   const char *scheme = std::getenv("LOS_PROJ_SCHEME");
-  const bool desc = !(scheme && std::atoi(scheme) == 0);
+  const bool desc = f32 || !(scheme && std::atoi(scheme) == 0);
   if (!desc && kernel_mask != 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project: the E-mode kernel needs the sweep scheme");
   los::SweepShape sw{};
@@ -396,10 +402,10 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
   a.S = (const double *)S;
   a.delta = (double *)delta;
   a.emask = kernel_mask;
-  hipError_t e = desc ? los::project_sweep_launch(a, nsrc, sw, false, (hipStream_t)stream)
+  hipError_t e = desc ? los::project_sweep_launch(a, nsrc, sw, f32, (hipStream_t)stream)
                       : los::project_fp64_launch(a, nsrc, sh, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "los_project launch");
-  const int rc = los::check_result("los_project", delta, nk * (int64_t)a.nl * nsrc, false,
+  const int rc = los::check_result("los_project", delta, nk * (int64_t)a.nl * nsrc, f32,
                                    (hipStream_t)stream);
   return rc == LOS_OK ? ok() : rc;
 }
