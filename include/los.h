@@ -246,8 +246,8 @@ int cl_integrate_noalloc(los_ctx *ctx, const void *delta, int32_t delta_prec, in
  *     delta[(i * nls + j) * nsrc + s] = Delta^s_{ls[j]}(k_i).
  *   ls: HOST, nls int32 strictly increasing within [lmin, lmax],
  *   1 <= nls <= lmax - lmin + 1.  The Bessel recurrence still walks every
- *   multipole (it needs them all); the accumulation, the reduction and the
- *   stores happen at the sampled ones only.  Other arguments, limits and
+ *   multipole (it needs them all); where a 16-row block holds at most 4 sampled
+ *   rows the accumulation, the reduction and the stores happen at those only.  Other arguments, limits and
  *   kernel_mask as for los_project_kernels.  The row tables built from ls are
  *   kept in the context; a call with a different list than the previous one
  *   waits for the work queued on `stream` before replacing them.

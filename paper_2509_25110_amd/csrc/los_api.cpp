@@ -501,10 +501,11 @@ int los_project_lsample(los_ctx *ctx, int32_t lmin, int32_t lmax, const int32_t 
   const char *scheme = std::getenv("LOS_PROJ_SCHEME");
   if (scheme && std::atoi(scheme) == 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project_lsample: needs the sweep scheme");
+  const int nl = lmax - lmin + 1, nblk = (nl + 15) / 16;
+  const bool every = nls == nl;  // every multipole: the dense sweep, same output
   const los::SweepShape sh = los::project_sweep_shape(nsrc, nk, ntau, env_int("LOS_PROJ_WAVES"));
   // device tables (output row per multipole, sampled-row mask per 16-row
   // block), rebuilt only when the list changes
-  const int nl = lmax - lmin + 1, nblk = (nl + 15) / 16;
   const size_t bytes = sizeof(int32_t) * (size_t)nl + sizeof(uint32_t) * (size_t)nblk;
   hipStream_t st = (hipStream_t)stream;
   std::vector<int32_t> key;
@@ -513,7 +514,7 @@ int los_project_lsample(los_ctx *ctx, int32_t lmin, int32_t lmax, const int32_t 
   key.push_back(lmax);
   key.insert(key.end(), ls, ls + nls);
   void *ws = ctx->ws[WS_LSEL];
-  if (key != ctx->lsel_key || ctx->ws_bytes[WS_LSEL] < bytes) {
+  if (!every && (key != ctx->lsel_key || ctx->ws_bytes[WS_LSEL] < bytes)) {
     std::vector<int32_t> lsel((size_t)nl, -1);
     std::vector<uint32_t> bmask((size_t)nblk, 0u);
     for (int32_t i = 0; i < nls; ++i) {
@@ -548,9 +549,11 @@ int los_project_lsample(los_ctx *ctx, int32_t lmin, int32_t lmax, const int32_t 
   a.S = S;
   a.delta = delta;
   a.emask = kernel_mask;
-  a.lsel = (const int32_t *)ws;
-  a.bmask = (const uint32_t *)((const char *)ws + sizeof(int32_t) * (size_t)nl);
-  a.nls = nls;
+  if (!every) {
+    a.lsel = (const int32_t *)ws;
+    a.bmask = (const uint32_t *)((const char *)ws + sizeof(int32_t) * (size_t)nl);
+    a.nls = nls;
+  }
   hipError_t e = los::project_sweep_launch(a, nsrc, sh, false, st);
   if (e != hipSuccess) return hip_fail(e, "los_project_lsample launch");
   const int rc2 = los::check_result("los_project_lsample", delta, nk * (int64_t)nls * nsrc, false, st);

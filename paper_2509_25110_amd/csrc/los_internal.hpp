@@ -28,7 +28,7 @@ struct ProjectArgs {
   uint32_t x1mask = 0, x2mask = 0;
   int splane[4] = {0, 1, 2, 3};
   // Multipole sampling (sweep kernel, 16-row blocks): when lsel is set, only
-  // rows l with lsel[l - lmin] >= 0 are accumulated and stored, at output
+  // rows l with lsel[l - lmin] >= 0 are stored, at output
   // row lsel[l - lmin] of delta[k][nls][nsrc]; bmask[bi] has bit r set when
   // row lmin + 16 bi + r is sampled.
   const int32_t *lsel = nullptr;

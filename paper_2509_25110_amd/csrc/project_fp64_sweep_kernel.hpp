@@ -48,6 +48,8 @@
 #include "fp64_common.hpp"
 #include "los_internal.hpp"
 
+#include <type_traits>
+
 namespace los {
 namespace sweep {
 
@@ -81,6 +83,35 @@ __device__ __forceinline__ void sweep_slot(double (&acc)[B * NSRC], double &p1, 
   }
 }
 
+// Sampled multipoles: C sampled rows of a block, off[r] rows below its top (uniform).  The
+// recurrence alone runs through the block (2 FP64 instructions a row instead of 2 + NSRC), its
+// 16 values stay in registers and the sampled ones are picked by a uniform index; no branch.
+// C2 at 91 multipoles: 1.87 -> 1.46 ms a pass against sweeping every block densely.  (A test per row in sweep_slot costs the compiler 300 spilled registers; runs from sample to
+// sample with loops in between were no faster than the dense sweep: 80 scalar instructions
+// and 20 branches a slot.)
+template <int NSRC, int C, int N>
+__device__ __forceinline__ void sampled_slot(double (&acc)[N], double &p1,
+                                             double &p0, double ix, const double (&sv)[NSRC],
+                                             int top, const int (&off)[C ? C : 1]) {
+  double t = 0.0, P[B];
+  const double d2 = ix + ix;
+#pragma unroll
+  for (int i = 0; i < B; ++i) {
+    if (i % 8 == 0) t = (double)(2 * (top - i) + 1) * ix;
+    P[i] = p0;
+    const double nx = rec_step(t, p0, p1);
+    p1 = p0;
+    p0 = nx;
+    t -= d2;
+  }
+#pragma unroll
+  for (int r = 0; r < C; ++r) {
+    const double v = P[off[r]];
+#pragma unroll
+    for (int s = 0; s < NSRC; ++s) acc[r * NSRC + s] = fma(v, sv[s], acc[r * NSRC + s]);
+  }
+}
+
 // Orders a wave's LDS accesses and keeps its lanes together: a wave's LDS operations are
 // performed in order, so no wait is needed, but the compiler must neither move accesses
 // across this point nor let one side of a divergent branch run ahead of it.
@@ -89,17 +120,18 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// A block's NV = 16 NSRC sums over a wave's lanes.  Two exchange steps (lanes 32 and 16
-// apart) leave NV / 4 values per lane, summed over 4 lanes; these go through the wave's LDS
+// NV values summed over a wave's lanes (16 NSRC for a whole block).  Two exchange steps
+// (lanes 32 and 16 apart) leave NV / 4 values per lane, summed over 4 lanes; these go through the wave's LDS
 // stage, [16][NV / H + 1] (the pad keeps both its accesses free of bank conflicts), in H
 // rounds.  f(e, total) is called by the lane that holds the total of value e.  Two rounds
 // (from 2 columns on) halve the stage, which decides how many waves fit a CU's LDS.
-constexpr int reduce_rounds(int nsrc) { return nsrc == 1 ? 1 : 2; }
-constexpr int stage_doubles(int nsrc) { return 16 * (B * nsrc / reduce_rounds(nsrc) + 1); }
+constexpr int reduce_rounds(int nv) { return nv <= 16 ? 1 : 2; }
+constexpr int stage_doubles(int nsrc) { return 16 * (B * nsrc / reduce_rounds(B * nsrc) + 1); }
 
-template <int NSRC, typename F>
-__device__ __forceinline__ void reduce_block(double (&v)[B * NSRC], double *stage, int lane, F f) {
-  constexpr int NV = B * NSRC, H = reduce_rounds(NSRC), P = NV / 4 / H, LD = NV / H + 1;
+template <int NV, typename F>
+__device__ __forceinline__ void reduce_block(double (&v)[NV], double *stage, int lane, F f) {
+  constexpr int H = reduce_rounds(NV), P = NV / 4 / H, LD = NV / H + 1;
+  static_assert(NV % (4 * H) == 0, "whole rounds");
   double u[NV / 2], q[NV / 4];
 #pragma unroll
   for (int p = 0; p < NV / 2; ++p) u[p] = fp64::swap_add32(v[p], v[p + NV / 2]);
@@ -161,8 +193,8 @@ __global__ void __launch_bounds__(64 * max_waves(NSRC)) project_fp64_sweep_kerne
   double2 *st = (double2 *)(ixs + npad);            // [npad] (w j_l, w j_{l+1}) at the next row
   double *stages = ixs + 3 * npad, *stage = stages + w * stage_doubles(NSRC);  // per wave
   short *rb = (short *)(stages + W * stage_doubles(NSRC));  // [npad] block of R
-  short *thA = rb + npad, *thF = thA + nslot;       // per slot: live / fully live up to this block
-  int *prog = (int *)(thF + nslot);                 // [W] progress of each wave
+  short *th = rb + npad, *tf = th + nslot;          // per slot: live / every lane live up to here
+  int *prog = (int *)(tf + nslot);                  // [W] progress of each wave
 
   const double kk = a.k[ki];
   const T *srow[NSRC];
@@ -226,17 +258,17 @@ __global__ void __launch_bounds__(64 * max_waves(NSRC)) project_fp64_sweep_kerne
     ixs[i] = ix;
     rb[i] = (short)(tiny ? kTinyNode : b);
     if (lane == 0) {
-      thA[s] = (short)bmax;
-      thF[s] = (short)bmin;
+      th[s] = (short)bmax;
+      tf[s] = (short)bmin;
     }
   }
   if (lane == 0) prog[w] = 0;
   __syncthreads();
 
   // Slot thresholds, lane j holding slots j and 64 + j; the highest live block.
-  const int tA0 = lane < nslot ? thA[lane] : -1, tA1 = lane + 64 < nslot ? thA[lane + 64] : -1;
-  const int tF0 = lane < nslot ? thF[lane] : -1, tF1 = lane + 64 < nslot ? thF[lane + 64] : -1;
-  int first = wave_max(tA0 > tA1 ? tA0 : tA1);
+  const int th0 = lane < nslot ? th[lane] : -1, th1 = lane + 64 < nslot ? th[lane + 64] : -1;
+  const int tf0 = lane < nslot ? tf[lane] : -1, tf1 = lane + 64 < nslot ? tf[lane + 64] : -1;
+  int first = wave_max(th0 > th1 ? th0 : th1);
 
   T *drow = (T *)a.delta + ki * (int64_t)(SMP ? a.nls : a.nl) * NSRC;
   // output offset of row l = b + e / NSRC, source e % NSRC (-1: not stored)
@@ -263,73 +295,76 @@ __global__ void __launch_bounds__(64 * max_waves(NSRC)) project_fp64_sweep_kerne
   const unsigned last = (unsigned)(ncnt - 1) * (unsigned)sizeof(T);
   for (int bi = first - w; bi >= 0; bi -= W, ++it) {
     const int b = lmin + bi * B, top = b + B - 1;
-    SlotList live{__ballot(tA0 >= bi), __ballot(tA1 >= bi)};
-    const uint64_t fullA = __ballot(tF0 >= bi), fullB = __ballot(tF1 >= bi);  // every lane live
+    const SlotList slots{__ballot(th0 >= bi), __ballot(th1 >= bi)};  // live in this block
+    const uint64_t fullA = __ballot(tf0 >= bi), fullB = __ballot(tf1 >= bi);  // every lane live
     // progress the wave above must have reached for slot s: 128 a block, s + 1 within it;
     // the top block waits for nobody
     const int base = w > 0 ? it * 128 : (it - 1) * 128;
-    const uint32_t rows = SMP ? a.bmask[bi] : 0xffffu;  // sampled rows (bit r: row b + r)
-    double acc[NV];
+    // Every live slot in order: body(p1, p0, ix, sv) takes the lane's pair through the block.
+    // sum: it uses the sources.
+    auto walk = [&](bool sum, auto body) {
+      SlotList live = slots;
+      auto load = [&](T (&sv)[NSRC], int s) {
+        if (!sum) return;  // uniform
+        unsigned off = (unsigned)(s * 64 + lane) * (unsigned)sizeof(T);
+        off = off < last ? off : last;  // lanes past the end read the last node (not used)
 #pragma unroll
-    for (int q = 0; q < NV; ++q) acc[q] = 0.0;
-    auto load = [&](T (&sv)[NSRC], int s) {
-      unsigned off = (unsigned)(s * 64 + lane) * (unsigned)sizeof(T);
-      off = off < last ? off : last;  // lanes past the end read the last node (not used)
-#pragma unroll
-      for (int q = 0; q < NSRC; ++q) sv[q] = *(const T *)((const char *)srow[q] + off);
-    };
-    auto step = [&](int s, const T (&raw)[NSRC], int snext) {
-      if (w > 0 || it > 0) {
-        const int need = base + s + 1;
-        while (known < need) {
-          known = __builtin_amdgcn_readfirstlane(
-              __hip_atomic_load(&prog[pred], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-          if (known < need) __builtin_amdgcn_s_sleep(1);
-        }
-        wave_sync();
-      }
-      const int i = s * 64 + lane;
-      if ((((s < 64 ? fullA : fullB) >> (s & 63)) & 1u) || rb[i] >= bi) {  // the node is live
-        const double2 pr = st[i];
-        const double ix = ixs[i];
-        double p0 = pr.x, p1 = pr.y;
-        double sv[NSRC];
-#pragma unroll
-        for (int q = 0; q < NSRC; ++q) sv[q] = (double)raw[q];
-        if (SC) {
-          const double i2 = ix * ix;
-#pragma unroll
-          for (int q = 0; q < NSRC; ++q) {
-            if (((a.emask | a.x2mask) >> q) & 1u) sv[q] *= i2;
-            else if ((a.x1mask >> q) & 1u) sv[q] *= ix;
+        for (int q = 0; q < NSRC; ++q) sv[q] = *(const T *)((const char *)srow[q] + off);
+      };
+      auto step = [&](int s, const T (&raw)[NSRC], int snext) {
+        if (w > 0 || it > 0) {
+          const int need = base + s + 1;
+          while (known < need) {
+            known = __builtin_amdgcn_readfirstlane(
+                __hip_atomic_load(&prog[pred], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+            if (known < need) __builtin_amdgcn_s_sleep(1);
           }
+          wave_sync();
         }
-        sweep_slot<NSRC>(acc, p1, p0, ix, sv, top);
-        st[i] = make_double2(p0, p1);
-      }
-      // the pairs are in place before the progress that announces them: every slot below
-      // the next live one is done
-      wave_sync();
-      __hip_atomic_store(&prog[w], snext >= 0 ? it * 128 + snext : (it + 1) * 128,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    // the next slot's sources are loaded while this one is swept
-    T sa[NSRC], sb[NSRC];
-    int s = live.pop();
-    if (s >= 0) load(sa, s);
-    while (s >= 0) {
-      const int s2 = live.pop();
-      if (s2 >= 0) load(sb, s2);
-      step(s, sa, s2);
-      if (s2 < 0) break;
-      s = live.pop();
+        const int i = s * 64 + lane;
+        if ((((s < 64 ? fullA : fullB) >> (s & 63)) & 1u) || rb[i] >= bi) {  // the node is live
+          const double2 pr = st[i];
+          const double ix = ixs[i];
+          double p0 = pr.x, p1 = pr.y;
+          double sv[NSRC];
+#pragma unroll
+          for (int q = 0; q < NSRC; ++q) sv[q] = (double)raw[q];
+          if (SC) {
+            const double i2 = ix * ix;
+#pragma unroll
+            for (int q = 0; q < NSRC; ++q) {
+              if (((a.emask | a.x2mask) >> q) & 1u) sv[q] *= i2;
+              else if ((a.x1mask >> q) & 1u) sv[q] *= ix;
+            }
+          }
+          body(p1, p0, ix, sv);
+          st[i] = make_double2(p0, p1);
+        }
+        // the pairs are in place before the progress that announces them: every slot below
+        // the next live one is done
+        wave_sync();
+        __hip_atomic_store(&prog[w], snext >= 0 ? it * 128 + snext : (it + 1) * 128,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      };
+      // the next slot's sources are loaded while this one is swept
+      T sa[NSRC] = {}, sb[NSRC] = {};
+      int s = live.pop();
       if (s >= 0) load(sa, s);
-      step(s2, sb, s);
-    }
-    if (SC && bi == 0 && (lim1 || lim2)) {
-      // Limits at x -> 0 of the scaled columns (the nodes below kXTiny are not swept):
-      // j_2(x)/x^2 -> 1/15 for E-mode and 1/x^2 columns at l = 2, j_1(x)/x -> 1/3 for
-      // 1/x columns at l = 1; every other row -> 0.
+      while (s >= 0) {
+        const int s2 = live.pop();
+        if (s2 >= 0) load(sb, s2);
+        step(s, sa, s2);
+        if (s2 < 0) break;
+        s = live.pop();
+        if (s >= 0) load(sa, s);
+        step(s2, sb, s);
+      }
+    };
+    // Limits at x -> 0 of the scaled columns (the nodes below kXTiny are not swept), for
+    // block 0: j_2(x)/x^2 -> 1/15 for E-mode and 1/x^2 columns at l = 2, j_1(x)/x -> 1/3
+    // for 1/x columns at l = 1; every other row -> 0.  add(row, q, term), row = l - lmin.
+    auto limits = [&](auto add) {
+      if (!SC || bi != 0 || !(lim1 || lim2)) return;
       const uint32_t m2 = a.emask | a.x2mask, m1 = a.x1mask;
       for (int sl = 0; sl < nslot; ++sl) {
         const int n = sl * 64 + lane;
@@ -337,25 +372,68 @@ __global__ void __launch_bounds__(64 * max_waves(NSRC)) project_fp64_sweep_kerne
         const double wn = a.w[n0 + n];
 #pragma unroll
         for (int q = 0; q < NSRC; ++q) {
-          const double e2 = lim2 && ((m2 >> q) & 1u) ? wn * (double)srow[q][n] * (1.0 / 15.0) : 0.0;
-          const double e1 = lim1 && ((m1 >> q) & 1u) ? wn * (double)srow[q][n] * (1.0 / 3.0) : 0.0;
-          if (lmin == 1) {
-            acc[q] += e1;         // row 1
-            acc[NSRC + q] += e2;  // row 2
-          } else {                // lmin == 2
-            acc[q] += e2;
-          }
+          if (lim2 && ((m2 >> q) & 1u)) add(2 - lmin, q, wn * (double)srow[q][n] * (1.0 / 15.0));
+          if (lim1 && ((m1 >> q) & 1u)) add(1 - lmin, q, wn * (double)srow[q][n] * (1.0 / 3.0));
         }
       }
-    }
-    if (rows == 0u) continue;  // no sampled row in this block (uniform)
-    reduce_block<NSRC>(acc, stage, lane, [&](int e, double tot) {
+    };
+    auto store = [&](int e, double tot) {
       const int l = b + e / NSRC;
       if (SC && ((a.emask >> (e % NSRC)) & 1u))
         tot *= sqrt((double)(l - 1) * (double)l * (double)(l + 1) * (double)(l + 2));
       const int64_t o = out_at(b, e);
       if (o >= 0) drow[o] = (T)(a.accumulate ? tot + (double)drow[o] : tot);
-    });
+    };
+    const uint32_t rows = SMP ? __builtin_amdgcn_readfirstlane(a.bmask[bi]) : 0xffffu;
+    const int nrow = __builtin_popcount(rows);
+    if (SMP && nrow <= 4) {  // few sampled rows (uniform)
+      auto few = [&](auto count) {
+        constexpr int C = decltype(count)::value, C1 = C ? C : 1;
+        constexpr int N = (C1 * NSRC + 3) / 4 * 4;  // (reduce_block takes multiples of 4)
+        int off[C1] = {};
+        uint32_t m = rows;  // bit r: row b + r
+#pragma unroll
+        for (int r = 0; r < C; ++r) {
+          off[r] = m ? __builtin_clz(m) - (32 - B) : B - 1;
+          m &= ~((1u << (B - 1)) >> off[r]);
+        }
+        double acc[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) acc[q] = 0.0;
+        walk(C > 0, [&](double &p1, double &p0, double ix, const double (&sv)[NSRC]) {
+          sampled_slot<NSRC, C>(acc, p1, p0, ix, sv, top, off);
+        });
+        if constexpr (C > 0) {
+          limits([&](int row, int q, double term) {
+#pragma unroll
+            for (int r = 0; r < C; ++r)
+              acc[r * NSRC + q] += r < nrow && off[r] == B - 1 - row ? term : 0.0;
+          });
+          reduce_block<N>(acc, stage, lane, [&](int e, double tot) {
+            int o = off[0];
+#pragma unroll
+            for (int r = 1; r < C; ++r) o = e / NSRC == r ? off[r] : o;
+            if (e / NSRC < nrow) store((B - 1 - o) * NSRC + e % NSRC, tot);
+          });
+        }
+      };
+      using std::integral_constant;
+      if (nrow == 0) few(integral_constant<int, 0>{});
+      else if (nrow == 1) few(integral_constant<int, 1>{});
+      else few(integral_constant<int, 4>{});
+    } else {
+      double acc[NV];
+#pragma unroll
+      for (int q = 0; q < NV; ++q) acc[q] = 0.0;
+      walk(true, [&](double &p1, double &p0, double ix, const double (&sv)[NSRC]) {
+        sweep_slot<NSRC>(acc, p1, p0, ix, sv, top);
+      });
+      limits([&](int row, int q, double term) {  // row 0 or 1
+        acc[q] += row == 0 ? term : 0.0;
+        acc[NSRC + q] += row == 1 ? term : 0.0;
+      });
+      reduce_block<NV>(acc, stage, lane, store);
+    }
   }
 }
 

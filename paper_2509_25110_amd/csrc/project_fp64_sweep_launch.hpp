@@ -28,19 +28,21 @@ hipError_t launch_t(const ProjectArgs &a, const SweepShape &sh, hipStream_t s) {
   return hipSuccess;
 }
 
+template <int NSRC, bool SC>
+hipError_t launch_f64(const ProjectArgs &a, const SweepShape &sh, hipStream_t s) {
+  if (!a.lsel) return launch_t<double, NSRC, false, SC>(a, sh, s);
+  if (!a.bmask) return hipErrorInvalidValue;
+  return launch_t<double, NSRC, true, SC>(a, sh, s);
+}
+
 template <int NSRC>
 hipError_t launch(const ProjectArgs &a, const SweepShape &sh, bool f32, bool scaled,
                   hipStream_t s) {
-  if (a.lsel && !a.bmask) return hipErrorInvalidValue;
   if (f32) {
     if (scaled || a.lsel) return hipErrorInvalidValue;
     return launch_t<float, NSRC, false, false>(a, sh, s);
   }
-  if (scaled)
-    return a.lsel ? launch_t<double, NSRC, true, true>(a, sh, s)
-                  : launch_t<double, NSRC, false, true>(a, sh, s);
-  return a.lsel ? launch_t<double, NSRC, true, false>(a, sh, s)
-                : launch_t<double, NSRC, false, false>(a, sh, s);
+  return scaled ? launch_f64<NSRC, true>(a, sh, s) : launch_f64<NSRC, false>(a, sh, s);
 }
 
 }  // namespace sweep

@@ -86,3 +86,28 @@ def test_nonfinite_sources_without_weight(torch_dev, ctx):
     S = wl.S.copy()
     S[:, :, 3], S[:, :, 70], S[:, :, 200], S[:, :, -1] = np.nan, np.inf, -np.inf, np.nan
     check(torch_dev, ctx, wl, S=S)
+
+
+@pytest.mark.parametrize("ls", [
+    [2, 3],                                   # first rows of the lowest block
+    [17, 18, 33, 49],                         # the ends of blocks
+    [5, 9, 11, 17, 21, 22, 23, 24, 25, 90],   # 3 in one block, 5 (the dense walk) in the next
+    [2, 5, 7, 8] + list(range(40, 120)),      # sparse and dense blocks
+    [119],
+])
+@pytest.mark.parametrize("mask", [0, 2])
+def test_sampled_rows_of_a_block(torch_dev, ctx, ls, mask):
+    """Blocks with 0, 1, 2..4 and more sampled rows, plain and E-mode (whose x -> 0 limit goes
+    to l = 2)."""
+    torch = torch_dev
+    dv = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    for nsrc in (2, 3, 4):
+        wl = workload(nsrc, lmax=119, nk=4, kmax=0.05, ntau=200)
+        d = ctx.los_project_lsample(wl.lmin, wl.lmax, ls, dv(wl.k), dv(wl.tau), wl.tau0,
+                                    dv(wl.w_tau), dv(wl.S), kernel_mask=mask)
+        torch.cuda.synchronize()
+        ref, A = oracle.project(wl.lmin, wl.lmax, wl.k, wl.tau, wl.tau0, wl.w_tau, wl.S,
+                                with_abs=True, eps_mask=mask)
+        sel = np.asarray(ls) - wl.lmin
+        scale = np.maximum(A.max(axis=0, keepdims=True), 1e-300)[:, sel]
+        assert float(np.max(np.abs(d.cpu().numpy() - ref[:, sel]) / scale)) <= 1e-10
