@@ -24,7 +24,7 @@ LIB = os.path.join(PKG, "liblos.so")
 # heaviest translation units first (the pool compiles them in this order)
 SOURCES = ["project_fp64_sweep_n4.hip", "project_fp64_sweep_n3.hip", "project_fp64_sweep_n2.hip",
            "project_fp64_sweep_n1.hip", "project_fp64.hip",
-           "emu_kernels.hip", "project_fused.hip", "project_mfma.hip", "project_mfma_lds.hip",
+           "emu_kernels.hip", "emu_gemm.hip", "project_fused.hip", "project_mfma.hip", "project_mfma_lds.hip",
            "spline.hip", "los_api.cpp", "batch_api.cpp", "emu_api.cpp", "bessel_table.hip",
            "project_fp64_sweep.hip", "cl_reduce.hip", "jtable.hip", "batch_cl.hip", "cl_interp.hip",
            "tensor.hip", "finite_check.hip"]

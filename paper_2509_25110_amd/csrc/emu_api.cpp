@@ -99,6 +99,32 @@ int nlayers(const los_emu *m) { return (int)m->sizes.size() - 1; }
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
 
+// Layer i of `members` networks from member e on (h [n][in] each, h_bs apart, to c [n][out]).
+E::GemmF32 layer(const los_emu *m, int e, int i, const float *h, int64_t h_bs, int64_t n, float *c,
+                 int members) {
+  const int64_t in = layer_in(m, i), o = layer_out(m, i);
+  const float *th = m->theta.as<float>() + (int64_t)e * m->nparams;
+  E::GemmF32 g{};
+  g.M = n;
+  g.N = o;
+  g.K = in;
+  g.A = h;
+  g.sam = in;
+  g.sak = 1;
+  g.B = th + m->woff[i];
+  g.sbk = 1;
+  g.sbn = in;
+  g.bias = th + m->woff[i] + o * in;
+  g.C = c;
+  g.ldc = o;
+  g.batch = members;
+  g.a_bs = h_bs;
+  g.b_bs = m->nparams;
+  g.c_bs = n * o;
+  g.bias_bs = m->nparams;
+  return g;
+}
+
 // Forward pass of member e on u [n][np]: activations act[i] [n][sizes[i]],
 // pre-activations pre[i]; the output goes to `out` [n][nout].
 int forward(los_emu *m, int e, const float *u, int64_t n, float *out, hipStream_t s) {
@@ -107,49 +133,55 @@ int forward(los_emu *m, int e, const float *u, int64_t n, float *out, hipStream_
   int rc = m->act.reserve(sizeof(float) * (size_t)n * wmax * (L + 1));
   if (rc == LOS_OK) rc = m->pre.reserve(sizeof(float) * (size_t)n * wmax * (L + 1));
   if (rc != LOS_OK) return rc;
-  const float *th = m->theta.as<float>() + (int64_t)e * m->nparams;
   const float *h = u;
   for (int i = 0; i < L; ++i) {
-    const int64_t in = layer_in(m, i), o = layer_out(m, i);
-    E::GemmF32 g{};
-    g.M = n;
-    g.N = o;
-    g.K = in;
-    g.A = h;
-    g.sam = in;
-    g.sak = 1;
-    g.B = th + m->woff[i];
-    g.sbk = 1;
-    g.sbn = in;
-    g.bias = th + m->woff[i] + o * in;
-    g.ldc = o;
+    float *c = i < L - 1 ? m->act.as<float>() + (int64_t)(i + 1) * n * wmax : out;
+    E::GemmF32 g = layer(m, e, i, h, 0, n, c, 1);
     if (i < L - 1) {
-      g.C = m->act.as<float>() + (int64_t)(i + 1) * n * wmax;
       g.Z = m->pre.as<float>() + (int64_t)i * n * wmax;
       HIPCHK(E::gemm_f32(g, E::kEpiBiasGelu, s), "emulator: layer GEMM");
-      h = g.C;
+      h = c;
     } else {
-      g.C = out;
       HIPCHK(E::gemm_f32(g, E::kEpiBias, s), "emulator: output GEMM");
     }
   }
   return LOS_OK;
 }
 
-// Loss and gradient of member e (after forward on the same u): dloss/dout is
-// in gbuf; gradient written to grad [nparams].
-int backward(los_emu *m, int e, const float *u, int64_t n, hipStream_t s) {
+// Every member on u [n][np], one launch per layer: the coefficients cz[e][n][nout], scaled
+// back by sigma (no pre-activations kept, two buffers of activations).
+int forward_members(los_emu *m, const float *u, int64_t n, float *cz, hipStream_t s) {
+  const int L = nlayers(m);
+  const int64_t per = (int64_t)m->members * n * m->width;
+  int rc = m->act.reserve(sizeof(float) * (size_t)(2 * per));
+  if (rc != LOS_OK) return rc;
+  const float *h = u;
+  int64_t h_bs = 0;  // the first layer's input is shared
+  for (int i = 0; i < L - 1; ++i) {
+    float *c = m->act.as<float>() + (i & 1) * per;
+    HIPCHK(E::gemm_f32(layer(m, 0, i, h, h_bs, n, c, m->members), E::kEpiBiasGelu, s),
+           "emulator: layer GEMM");
+    h = c;
+    h_bs = n * layer_out(m, i);
+  }
+  E::GemmF32 g = layer(m, 0, L - 1, h, h_bs, n, cz, m->members);
+  g.scale = m->sigma.as<double>();
+  HIPCHK(E::gemm_f32(g, E::kEpiBiasUnwhiten, s), "emulator: output GEMM");
+  return LOS_OK;
+}
+
+// Gradient of member e (after forward on the same u) into gr [nparams]; dloss/dout is in gbuf.
+int backward(los_emu *m, int e, const float *u, int64_t n, float *gr, hipStream_t s) {
   const int L = nlayers(m);
   const int64_t wmax = m->width > 0 ? m->width : 1;
   int rc = m->gbuf2.reserve(sizeof(float) * (size_t)n * std::max<int64_t>(wmax, m->nout));
   if (rc != LOS_OK) return rc;
   const float *th = m->theta.as<float>() + (int64_t)e * m->nparams;
-  float *gr = m->grad.as<float>();
   float *G = m->gbuf.as<float>(), *G2 = m->gbuf2.as<float>();
   for (int i = L - 1; i >= 0; --i) {
     const int64_t in = layer_in(m, i), o = layer_out(m, i);
     const float *h = i == 0 ? u : m->act.as<float>() + (int64_t)i * n * wmax;
-    E::GemmF32 g{};  // dW_i = G^T h
+    E::GemmF32 g{};  // dW_i = G^T h, db_i = the sums of G over the rows
     g.M = o;
     g.N = in;
     g.K = n;
@@ -161,32 +193,28 @@ int backward(los_emu *m, int e, const float *u, int64_t n, hipStream_t s) {
     g.sbn = 1;
     g.C = gr + m->woff[i];
     g.ldc = in;
-    HIPCHK(E::gemm_f32(g, E::kEpiStore, s), "emulator: weight gradient");
-    HIPCHK(E::colsum_f32(G, n, o, gr + m->woff[i] + o * in, s), "emulator: bias gradient");
-    if (i > 0) {
-      E::GemmF32 d{};  // G_prev = G W_i, then * gelu'(pre_{i-1})
-      d.M = n;
-      d.N = in;
-      d.K = o;
-      d.A = G;
-      d.sam = o;
-      d.sak = 1;
-      d.B = th + m->woff[i];
-      d.sbk = in;
-      d.sbn = 1;
-      d.C = G2;
-      d.ldc = in;
-      HIPCHK(E::gemm_f32(d, E::kEpiStore, s), "emulator: input gradient");
-      HIPCHK(E::gelu_backward(G2, m->pre.as<float>() + (int64_t)(i - 1) * n * wmax, n * in, s),
-             "emulator: GELU backward");
-      std::swap(G, G2);
-    }
+    g.rowsum = gr + m->woff[i] + o * in;
+    E::GemmF32 d{};  // G_prev = (G W_i) gelu'(pre_{i-1}); none below the first layer (M = 0)
+    d.M = i > 0 ? n : 0;
+    d.N = in;
+    d.K = o;
+    d.A = G;
+    d.sam = o;
+    d.sak = 1;
+    d.B = th + m->woff[i];
+    d.sbk = in;
+    d.sbn = 1;
+    d.C = G2;
+    d.ldc = in;
+    d.Z = i > 0 ? m->pre.as<float>() + (int64_t)(i - 1) * n * wmax : nullptr;
+    HIPCHK(E::gemm_backward(g, d, s), "emulator: layer gradients");
+    std::swap(G, G2);
   }
   return LOS_OK;
 }
 
 int loss_grad(los_emu *m, int e, const float *u, const float *z, int64_t n, float *loss,
-              int accumulate, hipStream_t s) {
+              int accumulate, float *grad, hipStream_t s) {
   int rc = m->ub.reserve(sizeof(float) * (size_t)n * m->nout);
   if (rc == LOS_OK) rc = m->gbuf.reserve(sizeof(float) * (size_t)n * std::max(m->width, m->nout));
   if (rc == LOS_OK) rc = m->part.reserve(sizeof(float) * (size_t)((n * m->nout + 255) / 256 + 1));
@@ -196,7 +224,7 @@ int loss_grad(los_emu *m, int e, const float *u, const float *z, int64_t n, floa
   HIPCHK(E::mse_grad(out, z, n * m->nout, m->gbuf.as<float>(), m->part.as<float>(), loss,
                      accumulate, s),
          "emulator: loss");
-  return backward(m, e, u, n, s);
+  return backward(m, e, u, n, grad, s);
 }
 
 // Glorot-uniform weights and zero biases of member e from SplitMix64.
@@ -245,7 +273,7 @@ int fit_member(los_emu *m, int e, const float *u, const float *z, int64_t n, int
       HIPCHK(E::gather_rows(u, ix, rows, m->np, m->ut.as<float>(), s), "emulator: gather");
       HIPCHK(E::gather_rows(z, ix, rows, m->nout, m->zt.as<float>(), s), "emulator: gather");
       rc = loss_grad(m, e, m->ut.as<float>(), m->zt.as<float>(), rows, m->loss.as<float>(),
-                     b > 0, s);
+                     b > 0, m->grad.as<float>(), s);
       if (rc != LOS_OK) return rc;
       ++t;
       const double sched = 0.01 + 0.99 * 0.5 * (1.0 + std::cos(M_PI * (double)(t - 1) / (double)T));
@@ -433,11 +461,8 @@ int emu_loss_grad(los_emu *emu, int32_t member, const float *u, const float *z, 
   if (!emu || !u || !z || !loss || !grad || n < 1 || member < 0 || member >= emu->members)
     return fail(LOS_ERR_INVALID, "emu_loss_grad: bad argument");
   hipStream_t s = (hipStream_t)stream;
-  int rc = loss_grad(emu, member, u, z, n, loss, 0, s);
-  if (rc != LOS_OK) return rc;
-  HIPCHK(hipMemcpyAsync(grad, emu->grad.p, sizeof(float) * emu->nparams, hipMemcpyDeviceToDevice, s),
-         "emu_loss_grad: copy");
-  return ok();
+  int rc = loss_grad(emu, member, u, z, n, loss, 0, grad, s);
+  return rc == LOS_OK ? ok() : rc;
 }
 
 int emu_fit(los_emu *emu, int32_t member, const float *u, const float *z, int64_t n,
@@ -533,7 +558,7 @@ int emu_train(los_emu *emu, const double *params, const double *lo, const double
   if ((rc = refresh_float_pca(m, s)) != LOS_OK) return rc;
   m->has_pca = true;
   HIPCHK(E::scale_params(params, n, m->np, m->lo.as<double>(), m->hi.as<double>(),
-                         m->cz.as<float>(), s),
+                         m->cz.as<float>(), nullptr, s),
          "emu_train: inputs");
   for (int e = 0; e < m->members; ++e) {
     if ((rc = init_member(m, e)) != LOS_OK) return rc;
@@ -553,40 +578,46 @@ static int infer(los_emu *emu, const char *who, const double *params, int64_t n,
   hipStream_t s = (hipStream_t)stream;
   los_emu *m = emu;
   const int64_t nl = m->nl;
+  const bool fused = m->members <= E::kMaxFused;
   int rc = m->ut.reserve(sizeof(float) * (size_t)n * m->np);
-  if (rc == LOS_OK) rc = m->zt.reserve(sizeof(float) * (size_t)n * m->nout);
-  if (rc == LOS_OK) rc = m->yall.reserve(sizeof(float) * (size_t)m->members * n * 4 * nl);
-  if (rc == LOS_OK) rc = m->cz.reserve(sizeof(float) * (size_t)n * std::max(m->ncomp, m->np));
+  if (rc == LOS_OK) rc = m->cz.reserve(sizeof(float) * (size_t)m->members * n * m->nout);
+  if (rc == LOS_OK && !fused)
+    rc = m->yall.reserve(sizeof(float) * (size_t)m->members * n * 4 * nl);
   if (rc == LOS_OK) rc = m->errb.reserve(sizeof(unsigned int) * 4 * (size_t)n);
   if (rc != LOS_OK) return rc;
+  unsigned int *bits = m->errb.as<unsigned int>();
+  float *cz = m->cz.as<float>();
   HIPCHK(E::scale_params(params, n, m->np, m->lo.as<double>(), m->hi.as<double>(),
-                         m->ut.as<float>(), s),
+                         m->ut.as<float>(), bits, s),
          "emu_infer: inputs");
-  for (int e = 0; e < m->members; ++e) {
-    if ((rc = forward(m, e, m->ut.as<float>(), n, m->zt.as<float>(), s)) != LOS_OK) return rc;
-    for (int sp = 0; sp < 4; ++sp) {
-      HIPCHK(E::unwhiten(m->zt.as<float>(), n, m->ncomp, sp, m->nout, m->sigma.as<double>(),
-                         m->cz.as<float>(), s),
-             "emu_infer: unwhiten");
-      E::GemmF32 g{};  // y = mean + cz basis^T
-      g.M = n;
-      g.N = nl;
-      g.K = m->ncomp;
-      g.A = m->cz.as<float>();
-      g.sam = m->ncomp;
-      g.sak = 1;
-      g.B = m->basis_f.as<float>() + (int64_t)sp * nl * m->ncomp;
-      g.sbk = 1;
-      g.sbn = m->ncomp;
-      g.C = m->yall.as<float>() + ((int64_t)e * n * 4 + sp) * nl;
-      g.ldc = 4 * nl;
-      g.bias = m->mean_f.as<float>() + (int64_t)sp * nl;
-      HIPCHK(E::gemm_f32(g, E::kEpiBias, s), "emu_infer: reconstruction");
-    }
+  if ((rc = forward_members(m, m->ut.as<float>(), n, cz, s)) != LOS_OK) return rc;
+  if (fused) {
+    HIPCHK(E::reconstruct_ensemble(cz, m->members, n, (int)nl, m->ncomp, m->basis_f.as<float>(),
+                                   m->mean_f.as<float>(), m->tscale.as<double>(), cl, bits, s),
+           "emu_infer: reconstruction");
+  } else {
+    for (int e = 0; e < m->members; ++e)
+      for (int sp = 0; sp < 4; ++sp) {
+        E::GemmF32 g{};  // y = mean + cz basis^T
+        g.M = n;
+        g.N = nl;
+        g.K = m->ncomp;
+        g.A = cz + ((int64_t)e * n * 4 + sp) * m->ncomp;
+        g.sam = m->nout;
+        g.sak = 1;
+        g.B = m->basis_f.as<float>() + (int64_t)sp * nl * m->ncomp;
+        g.sbk = 1;
+        g.sbn = m->ncomp;
+        g.C = m->yall.as<float>() + ((int64_t)e * n * 4 + sp) * nl;
+        g.ldc = 4 * nl;
+        g.bias = m->mean_f.as<float>() + (int64_t)sp * nl;
+        HIPCHK(E::gemm_f32(g, E::kEpiBias, s), "emu_infer: reconstruction");
+      }
+    HIPCHK(E::ensemble(m->yall.as<float>(), m->members, n, (int)nl, m->tscale.as<double>(), cl, bits,
+                       s),
+           "emu_infer: ensemble");
   }
-  HIPCHK(E::ensemble(m->yall.as<float>(), m->members, n, (int)nl, m->tscale.as<double>(), cl,
-                     m->errb.as<unsigned int>(), (float)threshold, err, need, err4, need4, s),
-         "emu_infer: ensemble");
+  HIPCHK(E::flags(bits, n, (float)threshold, err, need, err4, need4, s), "emu_infer: flags");
   rc = los::check_result(who, cl, n * 4 * nl, false, s);
   return rc == LOS_OK ? ok() : rc;
 }

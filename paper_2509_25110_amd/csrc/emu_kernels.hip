@@ -11,116 +11,7 @@ namespace los {
 namespace emu {
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-__device__ inline float gelu_f(float x) { return 0.5f * x * (1.f + erff(x * 0.70710678118654752f)); }
-__device__ inline float gelu_grad_f(float x) {
-  return 0.5f * (1.f + erff(x * 0.70710678118654752f)) +
-         x * expf(-0.5f * x * x) * 0.39894228040143268f;
-}
-
-// C(m, n) = sum_k A(m, k) B(k, n) with A(m, k) = A[m sam + k sak],
-// B(k, n) = B[k sbk + n sbn], C row-major with leading dimension ldc.
-// Workgroup: 64 x 64 of C, 4 waves in a 2 x 2 arrangement, each wave 32 x 32
-// (2 x 2 MFMA 16x16x4 blocks); rows and columns outside [M, N) and K beyond K
-// read 0.  K goes in tiles of 32: the workgroup stages the 64 x 32 slice of A
-// and the 32 x 64 slice of B in LDS, each loaded along whichever of its
-// strides is 1 (consecutive lanes, consecutive addresses), and loads the next
-// tile into registers while the matrix cores work on this one.  Every wave
-// issues its products in increasing k, 4 at a time.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
-  constexpr int KT = 32, LD = 80;  // row pitch: the 4 k rows of a read hit distinct banks
-  __shared__ float As[KT][LD], Bs[KT][LD];
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, lane = tid & 63;
-  const int r16 = lane & 15, kq = lane >> 4;
-  const int64_t mb = (int64_t)blockIdx.y * 64, nb = (int64_t)blockIdx.x * 64;
-  const int mw = (w >> 1) * 32, nw = (w & 1) * 32;
-  const int64_t m0 = mb + mw, n0 = nb + nw;
-  const bool a_k = g.sak == 1, b_n = g.sbn == 1;  // contiguous axis of each operand
-  // element it * 256 + tid of a tile: (row of A, k) and (k, column of B)
-  auto a_at = [&](int e, int &mm, int &kk) {
-    if (a_k) { kk = e & 31; mm = e >> 5; } else { mm = e & 63; kk = e >> 6; }
-  };
-  auto b_at = [&](int e, int &kk, int &nn) {
-    if (b_n) { nn = e & 63; kk = e >> 6; } else { kk = e & 31; nn = e >> 5; }
-  };
-  float ra[8], rb[8];
-  auto load = [&](int64_t k0) {
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int e = it * 256 + tid;
-      int mm, kk, nn, kb;
-      a_at(e, mm, kk);
-      b_at(e, kb, nn);
-      const int64_t m = mb + mm, ka = k0 + kk, n = nb + nn, kB = k0 + kb;
-      ra[it] = (m < g.M && ka < g.K) ? g.A[m * g.sam + ka * g.sak] : 0.f;
-      rb[it] = (n < g.N && kB < g.K) ? g.B[kB * g.sbk + n * g.sbn] : 0.f;
-    }
-  };
-  f4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  if (g.K > 0) load(0);
-  for (int64_t k0 = 0; k0 < g.K; k0 += KT) {
-    __syncthreads();  // the previous tile is consumed
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int e = it * 256 + tid;
-      int mm, kk, nn, kb;
-      a_at(e, mm, kk);
-      b_at(e, kb, nn);
-      As[kk][mm] = ra[it];
-      Bs[kb][nn] = rb[it];
-    }
-    __syncthreads();
-    if (k0 + KT < g.K) load(k0 + KT);
-    const int kn = g.K - k0 < KT ? (int)(g.K - k0) : KT;
-    for (int kk = 0; kk < kn; kk += 4) {
-      float a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        a[i] = As[kk + kq][mw + 16 * i + r16];
-        b[i] = Bs[kk + kq][nw + 16 * i + r16];
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int64_t n = n0 + 16 * j + r16;
-      if (n >= g.N) continue;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t m = m0 + 16 * i + 4 * kq + v;
-        if (m >= g.M) continue;
-        float x = acc[i][j][v];
-        float *c = g.C + m * g.ldc + n;
-        if (EPI == kEpiStore) {
-          *c = x;
-        } else if (EPI == kEpiAccumulate) {
-          *c += x;
-        } else if (EPI == kEpiBias) {
-          *c = x + g.bias[n];
-        } else {  // kEpiBiasGelu: keep the pre-activation in Z
-          x += g.bias[n];
-          g.Z[m * g.ldc + n] = x;
-          *c = gelu_f(x);
-        }
-      }
-    }
-}
-
-// FP64 C = A B (same strides as above), LDS-tiled 64 x 64 with a 4 x 4
+// FP64 C = A B (strides as in GemmF64), LDS-tiled 64 x 64 with a 4 x 4
 // register tile per thread; used for the PCA fit only.
 __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64 g) {
   __shared__ double As[16][65], Bs[16][65];
@@ -159,21 +50,6 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64 g) {
     }
 }
 
-// G <- G * gelu'(Z), elementwise.
-__global__ void gelu_backward_kernel(float *G, const float *Z, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) G[i] *= gelu_grad_f(Z[i]);
-}
-
-// out[c] = sum_r X[r * ld + c] (one thread per column, fixed order).
-__global__ void colsum_f32_kernel(const float *X, int64_t rows, int64_t cols, float *out) {
-  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.f;
-  for (int64_t r = 0; r < rows; ++r) s += X[r * cols + c];
-  out[c] = s;
-}
-
 // MSE gradient: G = 2 (out - z) / (n m); loss[0] = sum (out - z)^2 / (n m),
 // summed per block then added in block order by a single thread (fixed order).
 __global__ __launch_bounds__(256) void mse_grad_kernel(const float *out, const float *z, int64_t cnt,
@@ -194,11 +70,20 @@ __global__ __launch_bounds__(256) void mse_grad_kernel(const float *out, const f
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0] * scale;
 }
 
-__global__ void sum_partials_kernel(const float *partial, int nb, float *loss, int accumulate) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// One workgroup: thread i adds partials i, i + 256, ... in order, then a fixed tree.  (One
+// thread adding all of them took 30 us of a training step's 580.)
+__global__ __launch_bounds__(256) void sum_partials_kernel(const float *partial, int nb, float *loss,
+                                                           int accumulate) {
+  __shared__ float red[256];
   float s = 0.f;
-  for (int b = 0; b < nb; ++b) s += partial[b];
-  loss[0] = accumulate ? loss[0] + s : s;
+  for (int b = threadIdx.x; b < nb; b += 256) s += partial[b];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) loss[0] = accumulate ? loss[0] + red[0] : red[0];
 }
 
 // Adam with bias correction; lr already includes the schedule.
@@ -223,10 +108,11 @@ __global__ void gather_rows_kernel(const float *src, const int64_t *idx, int64_t
   dst[i] = src[idx[r] * cols + c];
 }
 
-// u = 2 (p - lo) / (hi - lo) - 1 in FP32.
+// u = 2 (p - lo) / (hi - lo) - 1 in FP32; err_bits (or NULL): 4 n words set to 0.
 __global__ void scale_params_kernel(const double *p, int64_t n, int np, const double *lo,
-                                    const double *hi, float *u) {
+                                    const double *hi, float *u, unsigned int *err_bits) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (err_bits && i < 4 * n) err_bits[i] = 0u;
   if (i >= n * np) return;
   const int j = (int)(i % np);
   u[i] = (float)(2.0 * (p[i] - lo[j]) / (hi[j] - lo[j]) - 1.0);
@@ -430,21 +316,8 @@ __global__ __launch_bounds__(256) void whiten_kernel(const double *c, int64_t n,
   for (int64_t r = 0; r < n; ++r) z[r * nout + s * ncomp + j] = (float)(c[r * ncomp + j] / scale);
 }
 
-// coefficient rows for reconstruction: cz[r][j] = out[r][s * ncomp + j] * sigma[s][j]
-__global__ void unwhiten_kernel(const float *out, int64_t n, int ncomp, int s, int nout,
-                                const double *sigma, float *cz) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n * ncomp) return;
-  const int64_t r = i / ncomp;
-  const int j = (int)(i % ncomp);
-  cz[i] = (float)((double)out[r * nout + s * ncomp + j] * sigma[s * ncomp + j]);
-}
-
-// Ensemble mean of C_l and error estimate.  y holds every member's
-// reconstructed transformed spectra, y[e][r][s][l] (float).  One thread per
-// (r, l): writes cl[r][s][l] (mean over members) for the 4 spectra and folds
-// the largest scaled deviation into err[r] (float bits, atomic max of
-// non-negative values: independent of order).
+// Ensemble of more than kMaxFused members (fewer: reconstruct_kernel), from every
+// member's reconstructed transformed spectra y[e][r][s][l] (float).  One thread per (r, l).
 // Member mean of every C_l and, per (row, spectrum), the largest member
 // deviation relative to the spectrum's scale (err_bits[r][4], float bits,
 // order-independent atomicMax).  Workgroup = one row r (blockIdx.x) and 256
@@ -512,41 +385,13 @@ __global__ void flag_kernel(const unsigned int *err_bits, int64_t n, float thr, 
   if (flag) flag[r] = !(emax <= thr);
 }
 
-__global__ void zero_u32_kernel(unsigned int *p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
-
 inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-hipError_t gemm_f32(const GemmF32 &g, int epi, hipStream_t s) {
-  dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64));
-  switch (epi) {
-    case kEpiStore: hipLaunchKernelGGL(gemm_f32_kernel<kEpiStore>, grid, dim3(256), 0, s, g); break;
-    case kEpiAccumulate:
-      hipLaunchKernelGGL(gemm_f32_kernel<kEpiAccumulate>, grid, dim3(256), 0, s, g);
-      break;
-    case kEpiBias: hipLaunchKernelGGL(gemm_f32_kernel<kEpiBias>, grid, dim3(256), 0, s, g); break;
-    default: hipLaunchKernelGGL(gemm_f32_kernel<kEpiBiasGelu>, grid, dim3(256), 0, s, g); break;
-  }
-  return hipGetLastError();
-}
-
 hipError_t gemm_f64(const GemmF64 &g, hipStream_t s) {
   dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64));
   hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), 0, s, g);
-  return hipGetLastError();
-}
-
-hipError_t gelu_backward(float *G, const float *Z, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(gelu_backward_kernel, dim3(blocks(n)), dim3(256), 0, s, G, Z, n);
-  return hipGetLastError();
-}
-
-hipError_t colsum_f32(const float *X, int64_t rows, int64_t cols, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(colsum_f32_kernel, dim3(blocks(cols)), dim3(256), 0, s, X, rows, cols, out);
   return hipGetLastError();
 }
 
@@ -555,7 +400,7 @@ hipError_t mse_grad(const float *out, const float *z, int64_t cnt, float *G, flo
   const unsigned nb = blocks(cnt);
   hipLaunchKernelGGL(mse_grad_kernel, dim3(nb), dim3(256), 0, s, out, z, cnt, 1.f / (float)cnt, G,
                      partial);
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(64), 0, s, partial, (int)nb, loss,
+  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, partial, (int)nb, loss,
                      accumulate);
   return hipGetLastError();
 }
@@ -577,9 +422,10 @@ hipError_t gather_rows(const float *src, const int64_t *idx, int64_t rows, int64
 }
 
 hipError_t scale_params(const double *p, int64_t n, int np, const double *lo, const double *hi,
-                        float *u, hipStream_t s) {
-  hipLaunchKernelGGL(scale_params_kernel, dim3(blocks(n * np)), dim3(256), 0, s, p, n, np, lo, hi,
-                     u);
+                        float *u, unsigned int *err_bits, hipStream_t s) {
+  const int64_t cnt = err_bits && np < 4 ? 4 * n : n * np;
+  hipLaunchKernelGGL(scale_params_kernel, dim3(blocks(cnt)), dim3(256), 0, s, p, n, np, lo, hi, u,
+                     err_bits);
   return hipGetLastError();
 }
 
@@ -617,21 +463,16 @@ hipError_t whiten(const double *c, int64_t n, int ncomp, int s_idx, int nout, do
   return hipGetLastError();
 }
 
-hipError_t unwhiten(const float *out, int64_t n, int ncomp, int s_idx, int nout,
-                    const double *sigma, float *cz, hipStream_t s) {
-  hipLaunchKernelGGL(unwhiten_kernel, dim3(blocks(n * ncomp)), dim3(256), 0, s, out, n, ncomp,
-                     s_idx, nout, sigma, cz);
+hipError_t ensemble(const float *y, int members, int64_t n, int nl, const double *t, double *cl,
+                    unsigned int *err_bits, hipStream_t s) {
+  if (n > 0x7fffffff) return hipErrorInvalidValue;  // one workgroup row per model row
+  hipLaunchKernelGGL(ensemble_kernel, dim3((unsigned)n, (unsigned)((nl + 255) / 256)), dim3(256), 0,
+                     s, y, members, n, nl, t, cl, err_bits);
   return hipGetLastError();
 }
 
-hipError_t ensemble(const float *y, int members, int64_t n, int nl, const double *t, double *cl,
-                    unsigned int *err_bits, float thr, float *err, unsigned char *flag,
-                    float *err4, unsigned char *flag4, hipStream_t s) {
-  hipLaunchKernelGGL(zero_u32_kernel, dim3(blocks(4 * n)), dim3(256), 0, s, err_bits, 4 * n);
-  if (n > 0x7fffffff) return hipErrorInvalidValue;  // one workgroup row per model row
-  if (n > 0 && nl > 0)
-    hipLaunchKernelGGL(ensemble_kernel, dim3((unsigned)n, (unsigned)((nl + 255) / 256)), dim3(256), 0,
-                       s, y, members, n, nl, t, cl, err_bits);
+hipError_t flags(const unsigned int *err_bits, int64_t n, float thr, float *err,
+                 unsigned char *flag, float *err4, unsigned char *flag4, hipStream_t s) {
   hipLaunchKernelGGL(flag_kernel, dim3(blocks(n)), dim3(256), 0, s, err_bits, n, thr, err, flag,
                      err4, flag4);
   return hipGetLastError();
