@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "emu_internal.hpp"
 
@@ -232,6 +233,50 @@ hipError_t launch_gemm(const GemmF32 &g, hipStream_t s) {
 
 // ------------------------------------------------ reconstruction and ensemble
 
+// 1 / k!
+__constant__ const double kInvFact[18] = {
+    1.0, 1.0, 0.5, 0.16666666666666666, 0.041666666666666664, 0.008333333333333333,
+    0.001388888888888889, 0.0001984126984126984, 2.48015873015873e-05, 2.7557319223985893e-06,
+    2.755731922398589e-07, 2.505210838544172e-08, 2.08767569878681e-09, 1.6059043836821613e-10,
+    1.1470745597729725e-11, 7.647163731819816e-13, 4.779477332387385e-14, 2.8114572543455206e-15};
+
+// Uniform coefficients by scalar loads: as literals they would sit in vector registers.
+typedef const __attribute__((address_space(4))) double *coef_ptr;
+__device__ inline coef_ptr inv_fact() {
+  coef_ptr p = (coef_ptr)(const double *)kInvFact;
+  asm volatile("" : "+s"(p));  // an address the compiler does not look through
+  return p;
+}
+
+// e^y: y = n ln 2 + r, |r| <= ln 2 / 2 (ln 2 in two parts), Taylor's polynomial of degree 13
+// (next term below 5e-18), scaled by 2^n; times 2^shift.  Below 1 unit in the last place;
+// overflows to inf, underflows to 0, NaN stays NaN.  About half the instructions of the
+// library's exp.
+__device__ __forceinline__ double exp_f64(double y, coef_ptr c, int shift = 0) {
+  y = y > 800.0 ? 800.0 : y;
+  y = y < -800.0 ? -800.0 : y;
+  const double n = rint(y * 1.4426950408889634);
+  double r = fma(-n, 0x1.62e42fefa3800p-1, y);
+  r = fma(-n, 0x1.ef35793c76730p-45, r);
+  double p = c[13];
+#pragma unroll
+  for (int k = 12; k >= 0; --k) p = fma(p, r, c[k]);
+  return ldexp(p, (int)n + shift);
+}
+
+// sinh y: (e^|y| - e^-|y|) / 2 from |y| = 1 on, Taylor's polynomial below (next term below
+// 9e-18 of y): within 2 units in the last place.  The library's sinh forms e^y in
+// double-double, 4 times the instructions.
+__device__ __forceinline__ double sinh_f64(double y, coef_ptr c) {
+  const double a = fabs(y), h = exp_f64(a, c, -1);  // e^|y| / 2, finite as long as sinh is
+  const double big = h - 0.25 / h;
+  const double y2 = y * y;
+  double p = c[17];
+#pragma unroll
+  for (int k = 15; k >= 1; k -= 2) p = fma(p, y2, c[k]);
+  return a < 1.0 ? y * p : copysign(big, y);
+}
+
 struct Recon {
   const float *cz;     // [MEM][n][4 nc]
   const float *basis;  // [4][nl][nc]
@@ -252,10 +297,11 @@ struct Recon {
 // memory (16 FP32 values per row and multipole at 4 members) they were written once and read
 // twice, and exp and sinh were taken twice.  The division by the scale is monotone, so the
 // largest |C_e - cl| is divided once.
-// Bound by the FP64 exp and sinh (VALU) beside the matrix cores; 4096 rows x 4999 multipoles
-// x 4 members: see the table kept with the measurements of this library.
+// Bound by the FP64 exp and sinh (VALU) beside the matrix cores: 4096 rows x 4999 multipoles
+// x 4 members take 1.25 ms (1.66 ms with the library's exp and sinh; three waves a SIMD,
+// 1.38 ms with two).
 template <int MEM, int WM, int WN>
-__global__ __launch_bounds__(256) void reconstruct_kernel(Recon a) {
+__global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
   constexpr int TM = 16 * WM, TN = 32 * WN, KT = 32, LD = KT + 4;
   typedef Operand<true, MEM * TM, KT, 256> OA;
   typedef Operand<true, TN, KT, 256> OB;
@@ -325,42 +371,49 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(Recon a) {
           }
         }
       }
+      // the spectrum's values: TE as t sinh(y), the others as exp(y)
+      auto finish = [&](auto te) {
+        constexpr bool TE = decltype(te)::value;
+        const coef_ptr ck = inv_fact();
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int64_t l = col0 + 32 * wn + 16 * j + r16;
-        const bool inl = l < a.nl;
-        const float mu = inl ? a.mean[(int64_t)sp * a.nl + l] : 0.f;
-        const double tl = inl && sp == 2 ? a.t[l] : 0.0;
+        for (int j = 0; j < 2; ++j) {
+          const int64_t l = col0 + 32 * wn + 16 * j + r16;
+          const bool inl = l < a.nl;
+          const float mu = inl ? a.mean[(int64_t)sp * a.nl + l] : 0.f;
+          const double tl = TE && inl ? a.t[l] : 0.0;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool in = inl && m0 + v < a.n;
-          if (!__any(in)) continue;
-          double c[MEM], mean = 0.0;
+          for (int v = 0; v < 4; ++v) {
+            const bool in = inl && m0 + v < a.n;
+            if (!__any(in)) continue;
+            double c[MEM], mean = 0.0;
 #pragma unroll
-          for (int e = 0; e < MEM; ++e) {
-            const double y = (double)(acc[e][j][v] + mu);
-            c[e] = sp == 2 ? tl * sinh(y) : exp(y);  // (uniform)
-            mean += c[e];
-          }
-          mean /= MEM;
-          double scale = fabs(mean);
-          if (sp == 0) keep[j][v] = mean;
-          if (sp == 1) keep[j][v] = sqrt(keep[j][v] * mean);
-          if (sp == 2) scale = keep[j][v];
-          double d = 0.0;
+            for (int e = 0; e < MEM; ++e) {
+              const double y = (double)(acc[e][j][v] + mu);
+              c[e] = TE ? tl * sinh_f64(y, ck) : exp_f64(y, ck);
+              mean += c[e];
+            }
+            mean /= MEM;
+            double scale = fabs(mean);
+            if (TE) scale = keep[j][v];
+            else if (sp == 0) keep[j][v] = mean;
+            else if (sp == 1) keep[j][v] = sqrt(keep[j][v] * mean);
+            double d = 0.0;
 #pragma unroll
-          for (int e = 0; e < MEM; ++e) d = fmax(d, fabs(c[e] - mean));
-          d = fmax(0.0, d / scale);
-          if (in) {
-            a.cl[((m0 + v) * 4 + sp) * a.nl + l] = mean;
-            const unsigned int bits = __float_as_uint((float)d);
-            // (worst[sp] with sp a constant: the array stays in registers)
+            for (int e = 0; e < MEM; ++e) d = fmax(d, fabs(c[e] - mean));
+            d = fmax(0.0, d / scale);
+            if (in) {
+              a.cl[((m0 + v) * 4 + sp) * a.nl + l] = mean;
+              const unsigned int bits = __float_as_uint((float)d);
+              // (worst[sp] with sp a constant: the array stays in registers)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (q == sp) worst[q][v] = bits > worst[q][v] ? bits : worst[q][v];
+              for (int q = 0; q < 4; ++q)
+                if (q == sp) worst[q][v] = bits > worst[q][v] ? bits : worst[q][v];
+            }
           }
         }
-      }
+      };
+      if (sp == 2) finish(std::true_type{});
+      else finish(std::false_type{});
     }
   }
   // the 16 lanes of a row, then one atomic per row and spectrum
