@@ -77,3 +77,31 @@ def test_gradient_edges(torch_dev, ctx, n, width, depth, ncomp):  # noqa: F811
     assert abs(float(loss.item()) - lref) <= 2e-5 * lref
     assert np.max(np.abs(grad.cpu().numpy() - gref)) <= 2e-5 * np.max(np.abs(gref))
     emu.close()
+
+
+def test_exp_sinh_range(torch_dev, ctx):  # noqa: F811
+    """With all weights zero the spectra are exp(mean) and t sinh(mean) of the FP32 means: within
+    2 units in the last place each (and one rounding by t), over the range where they are
+    finite, around sinh's change of form at 1, and at signed zeros."""
+    nl, ncomp = 4096, 8
+    emu = make_emu(ctx, nl=nl, ncomp=ncomp, width=16, depth=1, members=1)
+    sizes = eo.layer_sizes(5, 16, 1, 4 * ncomp)
+    emu.emu_set_params(0, np.zeros_like(glorot(np.random.default_rng(0), sizes)))
+    mu = np.zeros((4, nl), dtype=np.float32)
+    mu[0] = np.linspace(-708, 709, nl)
+    mu[1] = np.linspace(-1.5, 1.5, nl)
+    mu[2] = np.concatenate([np.linspace(-710.4, 710.4, nl // 2), np.linspace(-1.1, 1.1, nl // 4),
+                            np.geomspace(1e-30, 2, nl // 4)])
+    mu[3] = np.geomspace(1e-30, 700, nl)
+    mu[2, :2] = -0.0, 0.0
+    mu[3, :2] = -0.0, 0.0
+    t = np.full(nl, 0.75)
+    emu.emu_set_pca(-np.ones(5), np.ones(5), mu.astype(np.float64), np.zeros((4, nl, ncomp)),
+                    np.ones((4, ncomp)), t)
+    cl, _, _ = emu.emu_infer_spectra(dev(torch_dev, np.zeros((3, 5))), threshold=1e-3)
+    got = cl.cpu().numpy()
+    ref = np.exp(mu.astype(np.longdouble))
+    ref[2] = 0.75 * np.sinh(mu[2].astype(np.longdouble))
+    err = np.abs(got - ref) / np.maximum(np.abs(ref), np.finfo(np.float64).tiny)
+    assert np.max(err) <= 5 * 2.0 ** -53
+    emu.close()
