@@ -62,9 +62,8 @@ typedef enum {
     LOS_FP64 = 0,   /* IEEE double throughout                                 */
     LOS_FP32 = 1,   /* float data; on the matrix cores FP64 j_l rounded to FP32,
                        FP32 MFMA product, FP32 sum                             */
-    LOS_BF16X3 = 2  /* float data; on the matrix cores FP64 j_l rounded to FP32,
-                       split into bf16 hi + lo, three bf16 MFMA products, FP32
-                       sum                                                     */
+    LOS_BF16X3 = 2  /* float data; FP64 j_l rounded to FP32, split into bf16
+                       hi + lo; three bf16 MFMA products, FP32 sum             */
 } los_prec;
 
 typedef struct los_ctx los_ctx;
@@ -129,18 +128,18 @@ int los_bessel_table(los_ctx *ctx, const double *x, int64_t nx, int32_t lmin, in
  * LOS_FP64: the j_l are generated on the fly in registers (never stored) and
  * the band where |j_l| < ~1e-21 of its peak is skipped.
  * LOS_FP32 / LOS_BF16X3: float sources and delta.  With at most 4 columns per k the
- * same FP64 sweep is the fastest way, so by default both widen the sources as they
- * are read, form every j_l and every sum in FP64 and round delta once (no
- * workspace).  The matrix-core pipelines stay selectable by environment; they treat
- * Eq. 2-3 as the per-k matrix product Delta_k[l][s] = sum_n J_k[l][n] S[s][k][n],
- * J_k[l][n] = w_n j_l(k chi_n) computed in FP64 and rounded to FP32:
- * LOS_MIXED_FUSED=1 (or LOS_FUSED_SHAPE=<shape>) keeps the FP64 recurrence state
- * every 32 multipoles (a context workspace of at most LOS_JTAB_MIB MiB, environment,
- * default 4096, per chunk of k rows) and regenerates each tile of J_k from it in
- * on-chip memory, multiplying in the given precision with FP32 accumulation;
+ * same FP64 sweep is the fastest way, so LOS_FP32 widens the sources as they are
+ * read, forms every j_l and every sum in FP64 and rounds delta once (no workspace,
+ * expected C_l error ~1e-7 relative).  LOS_BF16X3, and LOS_FP32 when LOS_MIXED_FUSED
+ * or LOS_FUSED_SHAPE is set in the environment, run on the matrix cores (Eq. 2-3 as
+ * the per-k matrix product Delta_k[l][s] = sum_n J_k[l][n] S[s][k][n],
+ * J_k[l][n] = w_n j_l(k chi_n) computed in FP64 and rounded to FP32; expected C_l
+ * error ~1e-6): a first kernel keeps only the FP64 recurrence state every 32
+ * multipoles (a context workspace of at most LOS_JTAB_MIB MiB, environment, default
+ * 4096, per chunk of k rows) and the product kernel regenerates each tile of J_k from
+ * it in on-chip memory, multiplying in the given precision with FP32 accumulation;
  * LOS_MIXED_FUSED=0 selects whole FP32 tables in the workspace instead.  Those two
- * give the same values.  Expected C_l error: ~1e-7 relative by default, ~1e-6 on the
- * matrix cores (both precisions).
+ * give the same values.
  * Errors: LOS_ERR_OOM if the workspace cannot be allocated.
  */
 int los_project(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, int64_t ntau, double tau0,

@@ -165,7 +165,7 @@ los::GemmTile gemm_tile_for(int max_ncol) {
   return {2, 4};
 }
 
-// Mixed-precision projection on the matrix cores (LOS_MIXED_FUSED=1): per chunk of k rows the FP64
+// Mixed-precision projection on the matrix cores: per chunk of k rows the FP64
 // Bessel seeds (every 32 multipoles), then the product with the Bessel tiles
 // regenerated in LDS (project_fused.hip); no table reaches device memory.
 // The seed workspace is bounded by LOS_JTAB_MIB (default 4096 MiB);
@@ -349,14 +349,16 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
                 kernel_mask, nsrc);
   // Mixed precision: float sources and delta.  A k row has at most 4 columns, of which the
   // matrix cores use 16 at a time and for which they need every Bessel value generated, rounded
-  // and staged, so by default the FP64 sweep takes these too (widening the sources as it
-  // reads them): C3 in FP32 7.2 ms against 22.0 ms on the matrix cores, and no workspace.
-  // LOS_MIXED_FUSED or LOS_FUSED_SHAPE in the environment select the matrix-core pipelines.
+  // and staged, so for LOS_FP32 the FP64 sweep takes these too (widening the sources as it
+  // reads them): C3 7.2 ms against 22.0 ms on the matrix cores, and no workspace.  LOS_BF16X3
+  // names the split product itself, whose values a batch at that precision has to match, and
+  // stays on the matrix cores (C3 22.4 ms).  LOS_MIXED_FUSED or LOS_FUSED_SHAPE in the
+  // environment select the matrix-core pipelines for both.
   const bool f32 = prec != LOS_FP64;
   if (f32 && kernel_mask != 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project: the E-mode kernel is FP64 only");
   const char *fz = std::getenv("LOS_MIXED_FUSED");
-  if (f32 && (fz || std::getenv("LOS_FUSED_SHAPE"))) {
+  if (prec == LOS_BF16X3 || (f32 && (fz || std::getenv("LOS_FUSED_SHAPE")))) {
     const bool tables = fz && std::atoi(fz) == 0;
     int rc = tables ? project_mixed(ctx, lmin, lmax, nk, ntau, tau0, k, tau, w_tau,
                                     (const float *)S, nsrc, prec, (float *)delta,
