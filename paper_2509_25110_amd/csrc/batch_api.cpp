@@ -48,13 +48,15 @@ struct los_batch {
   // device
   int64_t *d_rows = nullptr, *d_col_off = nullptr, *d_pos_col = nullptr, *d_koff = nullptr,
           *d_jr = nullptr;
-  int *d_col_cnt = nullptr, *d_col_lmax = nullptr, *d_lmax = nullptr, *d_order = nullptr;
+  int *d_pos_row = nullptr, *d_col_cnt = nullptr, *d_col_lmax = nullptr, *d_lmax = nullptr, *d_order = nullptr;
   float *J = nullptr, *D = nullptr;
   int *top = nullptr;
   // fused pipeline: seeds workspace (J unused)
   bool fused = true;
   int nseg = 0;
   int64_t ntp64 = 0;
+  int64_t ldd = 0;  // column stride of D
+  int maxcol = 0;   // widest row
   void *seedws = nullptr;
   int fshape = 0;
   float ftune_ms[los::kFusedShapeCount] = {};
@@ -92,7 +94,7 @@ void free_plan(los_batch *b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   // `top` lives inside the J allocation
-  void *ptrs[] = {b->d_rows, b->d_col_off, b->d_pos_col, b->d_koff, b->d_jr, b->d_col_cnt,
+  void *ptrs[] = {b->d_rows, b->d_col_off, b->d_pos_col, b->d_pos_row, b->d_koff, b->d_jr, b->d_col_cnt,
                   b->d_col_lmax, b->d_lmax, b->d_order, b->J, b->D, b->seedws};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -240,7 +242,8 @@ los::FusedArgs fargs(const los_batch *b, const SolveArgs &s, int c) {
   a.k = s.k;
   a.tau = s.tau;
   a.w = s.w;
-  los::fused_workspace_at(a, b->seedws, (int)(b->chunk_row0[c + 1] - b->chunk_row0[c]));
+  los::fused_workspace_at(a, b->seedws, (int)(b->chunk_row0[c + 1] - b->chunk_row0[c]),
+                          b->maxcol);
   a.S = s.S;
   a.s_cstride = b->ntau;
   a.col_cnt = b->d_col_cnt;
@@ -248,7 +251,37 @@ los::FusedArgs fargs(const los_batch *b, const SolveArgs &s, int c) {
   a.col_base = b->chunk_col0[c];
   a.col_lmax = b->d_col_lmax;
   a.dtrans = 1;
+  a.ldd = b->ldd;
   a.delta = b->D;
+  return a;
+}
+
+los::BatchClArgs clargs(const los_batch *b, const SolveArgs &s, int c) {
+  los::BatchClArgs a{};
+  a.nmodels = b->nmodels;
+  a.nsrc = b->nsrc;
+  a.npairs = b->npairs;
+  a.lmin = b->lmin;
+  a.nl = b->nl;
+  a.chunk = c;
+  std::memcpy(a.pa, b->pa, sizeof a.pa);
+  std::memcpy(a.pb, b->pb, sizeof a.pb);
+  a.lmax = b->d_lmax;
+  a.koff = b->d_koff;
+  a.jr = b->d_jr;
+  a.order = b->d_order + (size_t)c * b->nmodels;
+  a.pos_col = b->d_pos_col;
+  a.col_base = b->chunk_col0[c];
+  a.ldd = b->ldd;
+  if (b->fused) {
+    a.pos_row = b->d_pos_row;
+    a.row_base = b->chunk_row0[c];
+    a.rowtop = fargs(b, s, c).rowtop;
+  }
+  a.D = b->D;
+  a.w_lnk = s.w_lnk;
+  a.Pk = s.Pk;
+  a.cl = s.cl;
   return a;
 }
 
@@ -279,33 +312,17 @@ int enqueue(los_batch *b, const SolveArgs &s, hipStream_t st) {
   for (int c = 0; c < b->nchunks; ++c) {
     int rc = enqueue_product(b, s, c, st);
     if (rc != LOS_OK) return rc;
-    los::BatchClArgs ca{};
-    ca.nmodels = b->nmodels;
-    ca.nsrc = b->nsrc;
-    ca.npairs = b->npairs;
-    ca.lmin = b->lmin;
-    ca.nl = b->nl;
-    ca.chunk = c;
-    std::memcpy(ca.pa, b->pa, sizeof ca.pa);
-    std::memcpy(ca.pb, b->pb, sizeof ca.pb);
-    ca.lmax = b->d_lmax;
-    ca.koff = b->d_koff;
-    ca.jr = b->d_jr;
-    ca.order = b->d_order + (size_t)c * b->nmodels;
-    ca.pos_col = b->d_pos_col;
-    ca.col_base = b->chunk_col0[c];
-    ca.D = b->D;
-    ca.w_lnk = s.w_lnk;
-    ca.Pk = s.Pk;
-    ca.cl = s.cl;
-    e = los::batch_cl_launch(ca, st);
+    e = los::batch_cl_launch(clargs(b, s, c), st);
     if (e != hipSuccess) return hip_fail(e, "los_batch_solve: C_l launch");
   }
   return LOS_OK;
 }
 
-// Fused pipeline: time the wide fused shapes (0..3) on two representative
-// chunks after building their seeds once; keep the fastest total.
+// Fused pipeline: time the wide fused shapes (0, 1, 3) and, up to 64 columns, the
+// 32-column one (three of its workgroups fit a CU, but past 64 columns it generates
+// every J three times) on two representative chunks after building their seeds once;
+// keep the fastest total.  7 models, at most 21 columns: shape 7 1.90 ms against 1.97
+// (1) and 1.93 (0); 48 models, 96 columns: shape 1 34.7 ms against 35.1 (0) and 37.7 (7).
 // LOS_BATCH_SHAPE pins a shape; LOS_BATCH_TUNE=0 keeps shape 0.
 int autotune_fused(los_batch *b, const SolveArgs &s, hipStream_t st) {
   const char *pin = std::getenv("LOS_BATCH_SHAPE");
@@ -336,9 +353,9 @@ int autotune_fused(los_batch *b, const SolveArgs &s, hipStream_t st) {
     (void)hipEventDestroy(t0);
     return hip_fail(e, "autotune: event");
   }
-  constexpr int kWide = 4;  // the shapes with at least 128 columns
-  constexpr int wide[kWide] = {0, 1, 2, 3};
-  float total[kWide] = {};
+  constexpr int wide[4] = {1, 0, 3, 7};
+  const int kWide = b->maxcol <= 64 ? 4 : 3;
+  float total[4] = {};
   int rc = LOS_OK;
   for (int pi = 0; pi < nprobe && rc == LOS_OK; ++pi) {
     const int c = probe[pi];
@@ -545,6 +562,7 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
   std::vector<int64_t> rows, col_off;
   std::vector<int> col_cnt, col_lmax;
   std::vector<int64_t> row_of_master(nk_master, -1);
+  std::vector<int> pos_row(b->npos);
   b->pos_col.assign(b->npos, 0);
   int64_t col = 0;
   for (int64_t K = 0; K < nk_master; ++K) {
@@ -556,6 +574,7 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
     col_cnt.push_back((int)((u1 - u0) * nsrc));
     for (int64_t u = u0; u < u1; ++u) {
       b->pos_col[row_pos[u]] = col;
+      pos_row[row_pos[u]] = (int)row_of_master[K];
       for (int s = 0; s < nsrc; ++s) col_lmax.push_back(lmax[row_models[u]]);
       col += nsrc;
     }
@@ -563,6 +582,7 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
   col_off.push_back(col);
   b->ncols = col;
   b->nrows = (int64_t)rows.size();
+  b->maxcol = *std::max_element(col_cnt.begin(), col_cnt.end());
 
   // chunks of rows.  Table pipeline: Bessel tables within LOS_JTAB_MIB
   // (default 4096 MiB).  Fused pipeline: seeds plus the chunk's products
@@ -572,8 +592,9 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
   b->fused = env_i("LOS_BATCH_FUSED", 1) != 0;
   b->nseg = (b->nlb + 1) / 2;
   b->ntp64 = (ntau + 63) / 64 * 64;
+  b->ldd = b->fused ? (b->nl + 31) / 32 * 32 : b->nl;
   const size_t jrow = sizeof(float) * (size_t)b->nlp * b->ntp + sizeof(int) * b->ntb;
-  const size_t srow = los::fused_seed_bytes_per_row(b->nseg, b->ntp64);
+  const size_t srow = los::fused_seed_bytes_per_row(b->nseg, b->ntp64, b->maxcol);
   size_t dmax = 0;
   if (b->fused) {
     int64_t mib = env_i("LOS_BATCH_MIB", 8192);
@@ -585,7 +606,7 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
       int64_t r1 = r0;
       size_t used = 0;
       while (r1 < b->nrows && r1 - r0 < 65535) {
-        const size_t add = srow + sizeof(float) * (size_t)col_cnt[r1] * b->nl;
+        const size_t add = srow + sizeof(float) * (size_t)col_cnt[r1] * b->ldd;
         if (r1 > r0 && used + add > budget) break;
         used += add;
         ++r1;
@@ -595,7 +616,7 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
       int mc = 0;
       for (int64_t r = r0; r < r1; ++r) mc = std::max(mc, col_cnt[r]);
       b->chunk_maxcol.push_back(mc);
-      dmax = std::max(dmax, (size_t)(col_off[r1] - col_off[r0]) * b->nl);
+      dmax = std::max(dmax, (size_t)(col_off[r1] - col_off[r0]) * b->ldd);
       b->kc = std::max(b->kc, r1 - r0);
       r0 = r1;
     }
@@ -611,7 +632,7 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
       int mc = 0;
       for (int64_t r = r0; r < r1; ++r) mc = std::max(mc, col_cnt[r]);
       b->chunk_maxcol.push_back(mc);
-      dmax = std::max(dmax, (size_t)(col_off[r1] - col_off[r0]) * b->nl);
+      dmax = std::max(dmax, (size_t)(col_off[r1] - col_off[r0]) * b->ldd);
     }
   }
   b->chunk_row0.push_back(b->nrows);
@@ -650,12 +671,13 @@ int los_batch_create(los_ctx *ctx, int32_t nmodels, int32_t nsrc, const int32_t 
   if (rc == LOS_OK) rc = dev_copy(&b->d_col_cnt, col_cnt.data(), col_cnt.size());
   if (rc == LOS_OK) rc = dev_copy(&b->d_col_lmax, col_lmax.data(), col_lmax.size());
   if (rc == LOS_OK) rc = dev_copy(&b->d_pos_col, b->pos_col.data(), b->pos_col.size());
+  if (rc == LOS_OK) rc = dev_copy(&b->d_pos_row, pos_row.data(), pos_row.size());
   if (rc == LOS_OK) rc = dev_copy(&b->d_koff, koff_v.data(), koff_v.size());
   if (rc == LOS_OK) rc = dev_copy(&b->d_lmax, lmax_v.data(), lmax_v.size());
   if (rc == LOS_OK) rc = dev_copy(&b->d_jr, jr.data(), jr.size());
   if (rc == LOS_OK) rc = dev_copy(&b->d_order, cl_order.data(), cl_order.size());
   if (rc == LOS_OK) {
-    hipError_t e = b->fused ? hipMalloc(&b->seedws, srow * (size_t)b->kc)
+    hipError_t e = b->fused ? hipMalloc(&b->seedws, los::kFusedFixedBytes + srow * (size_t)b->kc)
                             : hipMalloc((void **)&b->J, jrow * (size_t)b->kc);
     if (e == hipSuccess) e = hipMalloc((void **)&b->D, sizeof(float) * (dmax ? dmax : 1));
     if (e != hipSuccess) rc = fail(LOS_ERR_OOM, "los_batch_create: workspace: %s", hipGetErrorString(e));
@@ -797,26 +819,7 @@ int los_batch_solve_timed(los_batch *plan, double tau0, const double *k_master,
     }
     if (e == hipSuccess) e = hipEventRecord(ev[3 * c + 2], st);
     if (e != hipSuccess) break;
-    los::BatchClArgs ca{};
-    ca.nmodels = plan->nmodels;
-    ca.nsrc = plan->nsrc;
-    ca.npairs = plan->npairs;
-    ca.lmin = plan->lmin;
-    ca.nl = plan->nl;
-    ca.chunk = c;
-    std::memcpy(ca.pa, plan->pa, sizeof ca.pa);
-    std::memcpy(ca.pb, plan->pb, sizeof ca.pb);
-    ca.lmax = plan->d_lmax;
-    ca.koff = plan->d_koff;
-    ca.jr = plan->d_jr;
-    ca.order = plan->d_order + (size_t)c * plan->nmodels;
-    ca.pos_col = plan->d_pos_col;
-    ca.col_base = plan->chunk_col0[c];
-    ca.D = plan->D;
-    ca.w_lnk = w_lnk;
-    ca.Pk = Pk;
-    ca.cl = cl;
-    e = los::batch_cl_launch(ca, st);
+    e = los::batch_cl_launch(clargs(plan, s, c), st);
     if (e == hipSuccess) e = hipEventRecord(ev[3 * c + 3], st);
   }
   if (e == hipSuccess) e = hipEventSynchronize(ev.back());

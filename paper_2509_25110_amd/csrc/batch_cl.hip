@@ -22,11 +22,16 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(double *p, int64_t n) {
 // no other global load; the Delta values of four k are loaded before the first
 // of their terms is added.  Terms are accumulated per ordered source pair
 // (s, t) that some output pair uses, as (w P Delta_s) Delta_t in increasing j,
-// and each output pair reads its (s, t) sum at the end.
+// and each output pair reads its (s, t) sum at the end.  Where a row's band
+// ends below l (rowtop) Delta is zero and not stored: no load, and no term
+// unless w P is not finite.
 template <int NSRC>
 __global__ __launch_bounds__(256) void batch_cl_kernel(BatchClArgs a) {
   __shared__ int64_t s_col[256];
   __shared__ double s_wp[256];
+  __shared__ int s_top[256];
+  __shared__ int s_cnt[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = a.order[blockIdx.y];  // longest workgroups dispatched first
   const int lmax = a.lmax[m];
   if ((int)blockIdx.x * 256 + a.lmin > lmax) return;  // no multipole of this block
@@ -54,24 +59,53 @@ __global__ __launch_bounds__(256) void batch_cl_kernel(BatchClArgs a) {
   };
   const int64_t p0 = a.koff[m] + jlo;
   const float *D = a.D + lr;
+  const int l = lr + a.lmin;
   for (int64_t j0 = 0; j0 < jhi - jlo; j0 += 256) {
-    const int nb = (int)(jhi - jlo - j0 < 256 ? jhi - jlo - j0 : 256);
-    __syncthreads();  // the previous run's entries are consumed
+    int nb = (int)(jhi - jlo - j0 < 256 ? jhi - jlo - j0 : 256);
+    // the run's positions whose band reaches the block (the others add nothing unless w P is
+    // not finite), in order
+    bool keep = false;
+    int64_t col = 0;
+    double wp = 0.0;
+    int top = 0;
     if ((int)threadIdx.x < nb) {
       const int64_t p = p0 + j0 + threadIdx.x;
-      s_col[threadIdx.x] = (a.pos_col[p] - a.col_base) * (int64_t)a.nl;
-      s_wp[threadIdx.x] = a.w_lnk[p] * a.Pk[p];
+      top = a.rowtop ? a.rowtop[a.pos_row[p] - a.row_base] : lmax;
+      col = (a.pos_col[p] - a.col_base) * a.ldd;
+      wp = a.w_lnk[p] * a.Pk[p];
+      keep = top >= (int)blockIdx.x * 256 + a.lmin || wp * 0.0 != 0.0;
+    }
+    const uint64_t kept = __ballot(keep);
+    if (lane == 0) s_cnt[wave] = __popcll(kept);
+    __syncthreads();  // (and the previous run's entries are consumed)
+    int at = __popcll(kept & ((1ull << lane) - 1));
+    nb = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u < wave) at += s_cnt[u];
+      nb += s_cnt[u];
+    }
+    if (keep) {
+      s_col[at] = col;
+      s_wp[at] = wp;
+      s_top[at] = top;
     }
     __syncthreads();
     if (!live) continue;
+    // (past its row's band a column holds nothing: read and dropped, so that no load waits for
+    // a test)
     int i = 0;
     for (; i + 4 <= nb; i += 4) {
       double v[4][NSRC];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const float *d = D + s_col[i + u];
+        const bool in = l <= s_top[i + u];
 #pragma unroll
-        for (int s = 0; s < NSRC; ++s) v[u][s] = (double)d[(int64_t)s * a.nl];
+        for (int s = 0; s < NSRC; ++s) {
+          const float x = d[(int64_t)s * a.ldd];
+          v[u][s] = in ? (double)x : 0.0;
+        }
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) add_term(s_wp[i + u], v[u]);
@@ -80,7 +114,10 @@ __global__ __launch_bounds__(256) void batch_cl_kernel(BatchClArgs a) {
       const float *d = D + s_col[i];
       double v[NSRC];
 #pragma unroll
-      for (int s = 0; s < NSRC; ++s) v[s] = (double)d[(int64_t)s * a.nl];
+      for (int s = 0; s < NSRC; ++s) {
+        const float x = d[(int64_t)s * a.ldd];
+        v[s] = l <= s_top[i] ? (double)x : 0.0;
+      }
       add_term(s_wp[i], v);
     }
   }

@@ -138,6 +138,9 @@ struct FusedArgs {
   double *nix;                     // [kcount][ntp]
   int *rtop;                       // [kcount][ntp]
   int *cmax;                       // [kcount][ntp / 64] largest R of each chunk of 64 nodes
+  int *rowtop;                     // [kcount] largest R of the row
+  int2 *items;                     // tiles (l tile << 16 | chunk row, column tile) per XCD
+  int *queue;                      // [8][64] head and length of each XCD's list
   const float *S;
   int64_t s_kstride, s_cstride;
   int ncol;
@@ -145,24 +148,28 @@ struct FusedArgs {
   const int64_t *col_off;
   int64_t col_base;
   const int *col_lmax;
-  int dtrans;
+  int dtrans;                      // Delta transposed, rows above rowtop not written
+  int64_t ldd;                     // dtrans: column stride, a multiple of 32, >= 16 nlb
   float *delta;
 };
 struct FusedShape {
   int tm, tn;  // l rows x columns per workgroup
 };
-// Compiled shapes: 0 256x128 (waves 4x2), 1 128x128 (2x2), 2 256x128 (2x4),
-// 3 256x256 (2x4), 4 256x16 (8x1), 5 128x16 (4x1).
-constexpr int kFusedShapeCount = 6;
+// Compiled shapes: 0 and 2 256x128, 1 128x128, 3 256x256, 4 256x16, 5 128x16, 6 128x64,
+// 7 128x32.
+constexpr int kFusedShapeCount = 8;
 FusedShape fused_shape_at(int i);
-size_t fused_seed_bytes_per_row(int nseg, int64_t ntp);
-void fused_workspace_at(FusedArgs &a, void *ws, int kcount);
+// Workspace: kFusedFixedBytes + rows * fused_seed_bytes_per_row (rows of at most max_ncol columns).
+constexpr size_t kFusedFixedBytes = 2048;
+size_t fused_seed_bytes_per_row(int nseg, int64_t ntp, int max_ncol);
+void fused_workspace_at(FusedArgs &a, void *ws, int kcount, int max_ncol);
 hipError_t jseed_launch(const FusedArgs &a, int kcount, hipStream_t s);
 hipError_t fused_gemm_launch(const FusedArgs &a, int prec, int shape, int kcount, int max_ncol,
                              hipStream_t s);
 
 // Per-model C_l of a batch, one chunk of master rows at a time (batch_cl.hip).
-// D is the chunk's transposed product: D[(packed column - col_base) * nl + l - lmin].
+// D is the chunk's transposed product: D[(packed column - col_base) * ldd + l - lmin], for
+// l <= rowtop of the position's row (nullptr: every l); the rest is zero and not stored.
 struct BatchClArgs {
   int nmodels, nsrc, npairs, lmin, nl, chunk;
   int pa[16], pb[16];
@@ -172,6 +179,10 @@ struct BatchClArgs {
   const int *order;        // [nmodels] this chunk's models, the most rows first
   const int64_t *pos_col;  // [koff[nmodels]] packed column of (model, j), source 0
   int64_t col_base;
+  int64_t ldd;
+  const int *pos_row;      // [koff[nmodels]] plan row of (model, j)
+  int64_t row_base;        // plan row of rowtop[0]
+  const int *rowtop;
   const float *D;
   const double *w_lnk, *Pk;  // [koff[nmodels]]
   double *cl;                // [nmodels][npairs][nl]

@@ -10,8 +10,11 @@
 //   and R per node and the largest R of every chunk of 64 nodes.  Nothing of
 //   J itself is stored.
 //
-// fused_gemm_kernel (one workgroup per (k row, TM-row l tile, TN-column
-//   tile)): the tau axis advances in chunks of 64 nodes, visiting only the
+// tile_list_kernel: the (k row, TM-row l tile, TN-column tile) items that hold
+//   data, as one list per XCD.
+//
+// fused_gemm_kernel (as many workgroups as the device holds, each taking tiles
+//   from the lists): the tau axis advances in chunks of 64 nodes, visiting only the
 //   chunks whose largest R reaches the tile (two ballots over the chunk
 //   table), and the sources, seeds and R of the next such chunk are loaded
 //   while the matrix cores work on the current one.  Per chunk every
@@ -32,7 +35,28 @@
 //   seed[(kc * nseg + s) * ntp + n]    (w j_T, w j_{T+1}), T = min(R, lmin + 32 s + 31),
 //                                      written for segments with lmin + 32 s <= R
 //   cmax[kc * (ntp / 64) + c]          max of rtop over nodes 64 c .. 64 c + 63
+//   rowtop[kc]                         max of the row's cmax
+//   items, queue                       the tiles with data, per XCD, and the lists' heads
 // ntp = nodes padded to a multiple of 64 (at most 8192, so at most 128 chunks).
+//
+// What bounds it (48 models, 3 sources, l <= 5000, 8000 k, 3000 nodes; 84 to 102 columns a row):
+// in FP32 the matrix cores, 19 ms of the products' 31 at their peak rate; the rest is what two
+// workgroups a CU leave uncovered of the generation and staging.  One step of it was 51 ms, and
+//   54.1 -> 51.2 ms  column blocks dealt to the waves in turn; no S staged past the columns in use
+//   51.2 -> 41.1     tile lists and staying workgroups; rows above the band neither written nor
+//                    read
+//   41.1 -> 40.4     every wave takes all column blocks and two row blocks (2 x 2 waves with
+//                    half of each had 2 of 4 column blocks idle at 96 of 128 columns)
+//   40.4 -> 35.1     S and seed loads without tests or selects: the compiler had waited for them
+//                    before the products (vmcnt(0)) instead of after
+//   35.1 -> 33.9     a tile's column limits by one load; list heads on lines of their own
+// 7 models in split-BF16x3 (9 to 21 columns): 3.46 -> 1.51 ms.
+// Slower: S fragments from device memory straight to the lanes, no S in LDS (79 ms: each wave
+// loads them all, in half-used lines).
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
 #include "bessel_dev.hpp"
 #include "los_internal.hpp"
 
@@ -44,6 +68,7 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16;
 
 constexpr int KB = 64;  // tau nodes per LDS chunk
+constexpr int kQueueStride = 64;  // ints from one list's (head, length) to the next
 
 __device__ inline int wave_max_int(int v) {
 #pragma unroll
@@ -112,6 +137,77 @@ __global__ __launch_bounds__(256) void jseed_kernel(FusedArgs a) {
   if (bR == 0) sd[0] = make_double2(cur, nxt);
 }
 
+// ------------------------------------------------------------------ tile lists
+
+// Last 16-row l block that column c0 of plan row r, the largest l_max from there on, needs.
+__device__ inline int last_block(const FusedArgs &a, int64_t r, int c0) {
+  const int last = a.nlb - 1;
+  return a.col_lmax ? min(last, (a.col_lmax[a.col_off[r] + c0] - a.lmin) >> 4) : last;
+}
+
+// XCD x takes the rows of rank x, x + 8, ... (rank 0 = largest k, the most work): rows of the
+// lists before list x.
+__device__ inline int64_t list_base(int x, int kcount) {
+  return (int64_t)x * (kcount / 8) + min(x, kcount % 8);
+}
+
+// The tiles with anything to compute, as one list per XCD (workgroup x): largest k first; within
+// a row the l tiles of one column tile follow each other (they read the same S columns, kept in
+// that XCD's L2).  Also the row's band top, and the lists' heads and lengths for the product's
+// workgroups.  Launching a workgroup per possible tile instead left most of the chip idle where
+// few tiles hold data: the dispatcher deals workgroups to the shader engines in turn, and with an
+// even number of tiles a row the full ones all went to the same engines (48 models, 3 sources,
+// l <= 5000: the 900 smallest k, one full tile each, 1.38 ms; now 0.56 ms).
+__global__ __launch_bounds__(256) void tile_list_kernel(FusedArgs a, int tm, int tn, int tiles_m,
+                                                        int tiles_n, int kcount, int places) {
+  __shared__ int s_sum[4];
+  const int x = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int nch = (int)(a.ntp / KB);
+  const int rows = (kcount - x + 7) / 8;
+  int2 *out = a.items + list_base(x, kcount) * tiles_m * tiles_n;
+  int done = 0;
+  for (int i0 = 0; i0 < rows; i0 += 256) {
+    const bool in = i0 + tid < rows;
+    const int ki = kcount - 1 - (x + 8 * (i0 + tid));
+    int n = 0, top = -1, ncol = 0;
+    if (in) {
+      const int *cm = a.cmax + (int64_t)ki * nch;
+      for (int c = 0; c < nch; ++c) top = max(top, cm[c]);
+      a.rowtop[ki] = top;
+      // untransposed: every tile, those above the band write the zeros there
+      if (!a.dtrans) top = a.lmin + 16 * a.nlb - 1;
+      ncol = a.col_cnt ? a.col_cnt[a.k0 + ki] : a.ncol;
+      if (top >= a.lmin)
+        for (int c0 = 0; c0 < ncol; c0 += tn)
+          n += min(last_block(a, a.k0 + ki, c0), (top - a.lmin) >> 4) / (tm / 16) + 1;
+    }
+    int incl = n;  // inclusive sum over the wave
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    __syncthreads();  // the previous round's sums are read
+    if (lane == 63) s_sum[w] = incl;
+    __syncthreads();
+    int at = done + incl - n;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u < w) at += s_sum[u];
+      done += s_sum[u];
+    }
+    if (n > 0)
+      for (int c0 = 0; c0 < ncol; c0 += tn) {
+        const int m = min(last_block(a, a.k0 + ki, c0), (top - a.lmin) >> 4) / (tm / 16) + 1;
+        for (int u = 0; u < m; ++u) out[at++] = make_int2((int)((unsigned)u << 16 | ki), c0 / tn);
+      }
+  }
+  if (tid == 0) {
+    a.queue[kQueueStride * x] = places;
+    a.queue[kQueueStride * x + 1] = done;
+  }
+}
+
 // ------------------------------------------------------------------ product
 
 template <int PREC>
@@ -155,58 +251,74 @@ struct Stage {
   }
 };
 
-// A workgroup's tile: XCD x = L % 8 takes the rows of rank x, x + 8, ...
-// (rank 0 = largest k, the most work); within a row the l tiles of one column
-// tile follow each other (they read the same S columns, kept in that XCD's L2).
+// A workgroup's tile.
 struct Tile {
   int ki, tm, ncol, c0, lb0, lb_last, tile_lo, top_cap;
+  int nblk;  // 16-column blocks of the tile that need one of its rows (the first nblk)
   int64_t r, sbase, dbase;
 };
 
-// The tile (k rank kr, l tile tm, column tile tn); false when it has nothing
-// to compute (ki, r, tm, lb0 and tile_lo are set either way).
+// The tile (chunk row ki, l tile tm, column tile tn) of the list.  need: in lane j, the last
+// 16-row block (relative to the tile) that column block j needs, from the l_max of its first
+// column (columns are ordered by l_max, largest first, within a row); -1 where there is none.
+// (One load for all blocks: block after block they made 16 us of each 200 us tile.)
 template <int TM, int TN>
-__device__ inline bool tile_at(const FusedArgs &a, int kcount, int64_t kr, int tm, int tn, Tile &t) {
-  t.tm = tm;
-  t.ki = kcount - 1 - (int)kr;
+__device__ inline void tile_at(const FusedArgs &a, int ki, int tm, int tn, int lane, Tile &t,
+                               int &need) {
+  t.ki = ki;
   t.r = a.k0 + t.ki;
   t.lb0 = tm * (TM / 16);
+  t.tm = tm;
   t.tile_lo = 16 * t.lb0;  // first row of the tile (l - lmin)
-  t.ncol = a.col_cnt ? a.col_cnt[t.r] : a.ncol;
+  t.ncol = a.col_cnt ? __builtin_amdgcn_readfirstlane(a.col_cnt[t.r]) : a.ncol;
   t.c0 = tn * TN;
-  t.sbase = a.col_off ? a.col_off[t.r] * a.s_cstride : t.r * a.s_kstride;
-  t.dbase = a.col_off ? (a.col_off[t.r] - a.col_base) * (int64_t)a.nl
-                      : t.r * (int64_t)a.nl * t.ncol;
-  if (t.c0 >= t.ncol) return false;
-  t.lb_last = a.nlb - 1;
-  if (a.col_lmax) t.lb_last = min(t.lb_last, (a.col_lmax[a.col_off[t.r] + t.c0] - a.lmin) >> 4);
-  if (t.lb0 > t.lb_last) return false;
+  const int64_t off = a.col_off ? a.col_off[t.r] : 0;
+  t.sbase = a.col_off ? off * a.s_cstride : t.r * a.s_kstride;
+  t.dbase = a.col_off ? (off - a.col_base) * a.ldd : t.r * (int64_t)a.nl * t.ncol;
+  need = -1;
+  const int c = t.c0 + 16 * lane;
+  if (lane < TN / 16 && c < t.ncol)
+    need = (a.col_lmax ? min(a.nlb - 1, (a.col_lmax[off + c] - a.lmin) >> 4) : a.nlb - 1) - t.lb0;
+  t.nblk = (int)__popcll(__ballot(need >= 0));
+  t.lb_last = t.lb0 + __builtin_amdgcn_readfirstlane(need);
   t.top_cap = 16 * t.lb_last + 15 - t.tile_lo;  // last tile row any column needs
-  return true;
 }
 
-// The work item of this block: XCD x = L % 8 takes the rows of rank x, x + 8,
-// ... (rank 0 = largest k, the most work); within a row the l tiles of one
-// column tile follow each other (they read the same S columns, kept in that
-// XCD's L2).
-__device__ inline bool block_item(int tiles_m, int tiles_n, int kcount, int64_t &kr, int &tm,
-                                  int &tn) {
-  const int64_t per_row = (int64_t)tiles_m * tiles_n;
-  const int64_t L = blockIdx.x;
-  const int64_t q = L >> 3;
-  kr = (L & 7) + 8 * (q / per_row);
-  tm = (int)(q % per_row % tiles_m);
-  tn = (int)(q % per_row / tiles_m);
-  return kr < kcount;
+// A workgroup's tiles (thread 0 only).  The first is its own: workgroup 8 s + x of the launch has
+// place s of list x.  The rest of list x, from place gridDim.x / 8 on, and then of the other
+// lists, are taken as they come.  A list's head is read before it is raised, and each has a cache
+// line of its own: some hundred workgroups raising one line's heads at the end made 300 us.
+// Without lists (queue nullptr: a launch of at most one tile per workgroup whose empty tiles have
+// zeros to write) workgroup L has tile L.
+template <int TN>
+__device__ inline int2 first_tile(const FusedArgs &a, int per_row, int tiles_m, int kcount,
+                                  int &from) {
+  if (!a.queue) {
+    from = 8;
+    const int kr = blockIdx.x / per_row, u = blockIdx.x % per_row;
+    const int tn = u / tiles_m;
+    if (kr >= kcount || tn * TN >= a.ncol)
+      return make_int2(0, -1);
+    return make_int2((int)((unsigned)(u % tiles_m) << 16 | kr), tn);
+  }
+  const int x = blockIdx.x & 7, s = blockIdx.x >> 3;
+  if (s < a.queue[kQueueStride * x + 1]) return a.items[list_base(x, kcount) * per_row + s];
+  from = 8;  // list x has no more than one tile for each of its workgroups
+  return make_int2(0, -1);
 }
 
-template <int TM, int TN>
-__device__ inline bool tile_of_block(const FusedArgs &a, int tiles_m, int tiles_n, int kcount,
-                                     Tile &t) {
-  int64_t kr;
-  int tm, tn;
-  if (!block_item(tiles_m, tiles_n, kcount, kr, tm, tn)) return false;
-  return tile_at<TM, TN>(a, kcount, kr, tm, tn, t);
+__device__ inline int2 next_tile(const FusedArgs &a, int64_t per_row, int kcount, int &from) {
+  for (; from < 8; ++from) {
+    const int y = (blockIdx.x + from) & 7;
+    int *head = a.queue + kQueueStride * y;
+    const int len = head[1];
+    if (len <= (int)gridDim.x / 8 ||
+        __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= len)
+      continue;
+    const int q = atomicAdd(head, 1);
+    if (q < len) return a.items[list_base(y, kcount) * per_row + q];
+  }
+  return make_int2(0, -1);
 }
 
 // Active chunks: those whose largest top row reaches the tile's first row, as
@@ -249,14 +361,13 @@ struct ChunkIn {
   int R = -1;
   double2 sd = make_double2(0.0, 0.0);
   double nx = 0.0;
-  float4 sv[SPT];
+  f4 sv[SPT];
 };
 
 // What a producing wave needs to regenerate its segment and stage S.
 struct Producer {
   int seg_hi;         // l - lmin of the segment's top row
   bool seg_ok;        // the segment exists (sg < nseg)
-  bool s_vec;         // S columns are 16-byte aligned
   int64_t rowb;       // chunk row offset in the per-node tables
   const double2 *seedp;
 };
@@ -266,45 +377,37 @@ __device__ inline Producer producer_of(const FusedArgs &a, const Tile &t, int sg
   p.seg_ok = sg < a.nseg;
   p.seg_hi = 32 * sg + 31;
   p.rowb = (int64_t)t.ki * a.ntp;
-  p.seedp = a.seed + ((int64_t)t.ki * a.nseg + (p.seg_ok ? sg : 0)) * a.ntp;
-  p.s_vec = (a.s_cstride % 4 == 0) && (t.sbase % 4 == 0) && (a.ntau % 4 == 0);
+  p.seedp = a.seed + ((int64_t)t.ki * a.nseg + (p.seg_ok ? sg : a.nseg - 1)) * a.ntp;
   return p;
 }
 
-template <int TN, int NTH>
+typedef f4 f4_any __attribute__((aligned(4)));  // a 16-byte load at any float
+
+// No load here waits for another or is tested, and no value is touched, so that all are in
+// flight until gen_segment and store_s take them: columns past the blocks in use read the last
+// one (their products are not stored), and pieces that reach past tau the last four nodes
+// (those past it meet zeros in J, and a non-finite value has reached the sums from its own
+// node already).  TINY: fewer than 4 nodes, element by element.
+template <int TN, int NTH, bool TINY>
 __device__ inline void load_chunk_in(const FusedArgs &a, const Tile &t, const Producer &p, int c,
                                      int lane, int pt, ChunkIn<SPieces<TN, NTH>::SPT> &in) {
-  constexpr int SP = SPieces<TN, NTH>::SP, SPT = SPieces<TN, NTH>::SPT;
+  constexpr int SPT = SPieces<TN, NTH>::SPT;
   const int n = c * KB + lane;
   in.R = a.rtop[p.rowb + n];
   in.nx = a.nix[p.rowb + n];
-  if (p.seg_ok) in.sd = p.seedp[n];  // read whatever the node's R; used only below R
-  // A chunk wholly inside the tau grid with 16-byte aligned columns loads its
-  // pieces as 16-byte vectors with no branch (columns past ncol read column 0
-  // and are zeroed); the last, ragged chunk goes element by element.
-  if (p.s_vec && (c + 1) * KB <= a.ntau) {  // uniform
+  in.sd = p.seedp[n];  // read whatever the node's R; used only below R
+  const int last = (int)a.ntau - 1;
+  const int ns = c * KB + pt * 4 % KB;  // the piece's first node, and its column
+  const int cs = t.c0 + pt * 4 / KB, clast = min(t.c0 + 16 * t.nblk, t.ncol) - 1;
 #pragma unroll
-    for (int q = 0; q < SPT; ++q) {
-      if (SP % NTH != 0 && q * NTH + pt >= SP) break;
-      const int e = (q * NTH + pt) * 4;  // element within [TN][KB]
-      const int col = e / KB, nn = e % KB;
-      const int cg = t.c0 + col;
-      const float4 v = *(const float4 *)(a.S + t.sbase + (int64_t)(cg < t.ncol ? cg : 0) * a.s_cstride +
-                                         c * KB + nn);
-      in.sv[q] = cg < t.ncol ? v : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  } else {
+  for (int q = 0; q < SPT; ++q) {
+    const float *src =
+        a.S + t.sbase + (int64_t)min(cs + q * (NTH * 4 / KB), clast) * a.s_cstride;
+    if (TINY) {
 #pragma unroll
-    for (int q = 0; q < SPT; ++q) {
-      if (SP % NTH != 0 && q * NTH + pt >= SP) break;
-      const int e = (q * NTH + pt) * 4;
-      const int col = e / KB, nn = e % KB;
-      const int cg = t.c0 + col, ng = c * KB + nn;
-      const float *src = a.S + t.sbase + (int64_t)(cg < t.ncol ? cg : 0) * a.s_cstride + ng;
-      float t4[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) t4[u] = (cg < t.ncol && ng + u < a.ntau) ? src[u] : 0.f;
-      in.sv[q] = make_float4(t4[0], t4[1], t4[2], t4[3]);
+      for (int u = 0; u < 4; ++u) in.sv[q][u] = src[min(ns + u, last)];
+    } else {
+      in.sv[q] = *(const f4_any *)(src + min(ns, last - 3));
     }
   }
 }
@@ -353,20 +456,31 @@ __device__ inline void gen_segment(const FusedArgs &a, const Producer &p, const 
 }
 
 // The thread's S pieces into the stage (FP32, or split into bf16 hi and lo).
+// Pieces that cross the end of tau (over nodes past it, 1 to 3; 0: none in this chunk) were
+// read from the last four nodes and are shifted here, those from node `edge` on.
 template <int PREC, int TM, int TN, int NTH>
-__device__ inline void store_s(const ChunkIn<SPieces<TN, NTH>::SPT> &in, int pt,
-                               const Stage<PREC, TM, TN> &sm) {
+__device__ inline void store_s(ChunkIn<SPieces<TN, NTH>::SPT> &in, int nblk, int over, int edge,
+                               int pt, const Stage<PREC, TM, TN> &sm) {
+  if (over > 0) {  // uniform
+    const bool cross = pt * 4 % KB >= edge;
+    for (int o = 0; o < over; ++o)
+#pragma unroll
+      for (int q = 0; q < SPieces<TN, NTH>::SPT; ++q) {
+        const f4 v = in.sv[q];
+        in.sv[q] = cross ? f4{v[1], v[2], v[3], v[3]} : v;
+      }
+  }
   constexpr int LD = LdsLayout<PREC>::LD;
   constexpr int SP = SPieces<TN, NTH>::SP, SPT = SPieces<TN, NTH>::SPT;
 #pragma unroll
   for (int q = 0; q < SPT; ++q) {
-    if (SP % NTH != 0 && q * NTH + pt >= SP) break;
+    if (q * NTH >= nblk * 4 * KB || (SP % NTH != 0 && q * NTH + pt >= SP)) break;
     const int e = (q * NTH + pt) * 4;
     const int col = e / KB, nn = e % KB;
     if (PREC == 1) {
-      *(float4 *)(sm.Sf + col * LD + nn) = in.sv[q];
+      *(f4 *)(sm.Sf + col * LD + nn) = in.sv[q];
     } else {
-      const float v4[4] = {in.sv[q].x, in.sv[q].y, in.sv[q].z, in.sv[q].w};
+      const f4 v4 = in.sv[q];
       u16 hh[4], ll[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -382,237 +496,263 @@ __device__ inline void store_s(const ChunkIn<SPieces<TN, NTH>::SPT> &in, int pt,
   }
 }
 
-// Column blocks whose models stop below a row block skip its products: the
-// last 16-row block (relative to the tile) that column block j of the wave
-// needs, from the l_max of its first column (columns are ordered by l_max,
-// largest first, within a row).
-template <int NBW>
-__device__ inline void column_limits(const FusedArgs &a, const Tile &t, int wc, int (&jlast)[NBW]) {
-#pragma unroll
-  for (int j = 0; j < NBW; ++j) {
-    const int cj = t.c0 + wc * NBW * 16 + 16 * j;
-    jlast[j] = __builtin_amdgcn_readfirstlane(  // uniform
-        (a.col_lmax && cj < t.ncol) ? ((a.col_lmax[a.col_off[t.r] + cj] - a.lmin) >> 4) - t.lb0
-                                    : (cj < t.ncol ? a.nlb - 1 - t.lb0 : -1));
+// Products of one 32-node block of a wave's row blocks 0 .. M - 1 with a column block.
+template <int PREC>
+struct Frag;
+template <>
+struct Frag<1> {
+  float v[8];
+  __device__ void load(const float *hi, const float *, int ofs) {
+    const float4 a = *(const float4 *)(hi + ofs), b = *(const float4 *)(hi + ofs + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
   }
+};
+template <>
+struct Frag<2> {
+  bf8 h, l;
+  __device__ void load(const u16 *hi, const u16 *lo, int ofs) {
+    h = *(const bf8 *)(hi + ofs);
+    l = *(const bf8 *)(lo + ofs);
+  }
+};
+
+template <int M>
+__device__ __forceinline__ void products(f4 (&acc)[2], const Frag<1> (&a)[2], const Frag<1> &b) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].v[e], b.v[e], acc[i], 0, 0, 0);
+}
+template <int M>
+__device__ __forceinline__ void products(f4 (&acc)[2], const Frag<2> (&a)[2], const Frag<2> &b) {
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].l, b.h, acc[i], 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].h, b.l, acc[i], 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].h, b.h, acc[i], 0, 0, 0);
 }
 
-// One chunk's products for one multiplying wave: its row blocks are
-// bi = bofs + BSTR * i of the tile (those with data: 16 bi <= top_tr), its
-// column blocks wc * NBW + j; the two 32-node blocks of the chunk in
-// increasing order.  Every accumulator sees its terms in the same order
-// whichever wave owns it.
-template <int PREC, int TM, int TN, int MBW, int NBW, int BSTR>
-__device__ inline void mfma_chunk(f4 (&acc)[MBW][NBW], const int (&jlast)[NBW], int bofs, int wc,
-                                  int top_tr, int g, int r16, const Stage<PREC, TM, TN> &sm) {
+// One chunk's products for one wave: its row blocks are wr and wr + WR of the
+// tile (those with data: 16 wr <= top_tr), every column block in turn; the two
+// 32-node blocks of the chunk in increasing order.  Every accumulator sees its
+// terms in the same order whichever wave owns it.  A wave holds the fragments
+// of its rows and streams the columns', each read one block ahead.
+template <int PREC, int TM, int TN, int WR, int NB>
+__device__ inline void mfma_chunk(f4 (&acc)[NB][2], const int (&njb)[2], int wr, int top_tr, int g,
+                                  int r16, const Stage<PREC, TM, TN> &sm) {
   constexpr int LD = LdsLayout<PREC>::LD;
-  if (16 * bofs > top_tr) return;
+  const int n0 = 16 * wr <= top_tr ? njb[0] : 0;
+  const int n1 = 16 * (wr + WR) <= top_tr ? njb[1] : 0;  // <= n0
+  if (n0 == 0) return;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const int kofs = 32 * h + 8 * g;
-    if (PREC == 1) {
-      float bfv[NBW][8];
+    const int kofs = r16 * LD + 32 * h + 8 * g;
+    Frag<PREC> fa[2], fb[2];
 #pragma unroll
-      for (int j = 0; j < NBW; ++j) {
-        const float *src = sm.Sf + (wc * NBW * 16 + 16 * j + r16) * LD + kofs;
-        const float4 u = *(const float4 *)src, v = *(const float4 *)(src + 4);
-        bfv[j][0] = u.x; bfv[j][1] = u.y; bfv[j][2] = u.z; bfv[j][3] = u.w;
-        bfv[j][4] = v.x; bfv[j][5] = v.y; bfv[j][6] = v.z; bfv[j][7] = v.w;
-      }
+    for (int i = 0; i < 2; ++i) {
+      const int ofs = 16 * (wr + WR * i) * LD + kofs;
+      if constexpr (PREC == 1) fa[i].load(sm.Jf, nullptr, ofs);
+      else fa[i].load(sm.Jh, sm.Jl, ofs);
+    }
+    auto load_b = [&](int j) {
+      const int ofs = 16 * j * LD + kofs;
+      if constexpr (PREC == 1) fb[j & 1].load(sm.Sf, nullptr, ofs);
+      else fb[j & 1].load(sm.Sh, sm.Sl, ofs);
+    };
+    load_b(0);
 #pragma unroll
-      for (int i = 0; i < MBW; ++i) {
-        const int bi = bofs + BSTR * i;
-        if (16 * bi <= top_tr) {
-          const float *src = sm.Jf + (16 * bi + r16) * LD + kofs;
-          const float4 u = *(const float4 *)src, v = *(const float4 *)(src + 4);
-          const float af[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-          if (bi <= jlast[NBW - 1]) {  // every column block: accumulators in turn
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-              for (int j = 0; j < NBW; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[e], bfv[j][e], acc[i][j], 0, 0, 0);
-          } else {
-#pragma unroll
-            for (int j = 0; j < NBW; ++j)
-              if (bi <= jlast[j]) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                  acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[e], bfv[j][e], acc[i][j],
-                                                                   0, 0, 0);
-              }
-          }
-        }
-      }
-    } else {
-      bf8 bh[NBW], bl[NBW];
-#pragma unroll
-      for (int j = 0; j < NBW; ++j) {
-        const int row = wc * NBW * 16 + 16 * j + r16;
-        bh[j] = *(const bf8 *)(sm.Sh + row * LD + kofs);
-        bl[j] = *(const bf8 *)(sm.Sl + row * LD + kofs);
-      }
-#pragma unroll
-      for (int i = 0; i < MBW; ++i) {
-        const int bi = bofs + BSTR * i;
-        if (16 * bi <= top_tr) {
-          const int row = 16 * bi + r16;
-          const bf8 ah = *(const bf8 *)(sm.Jh + row * LD + kofs);
-          const bf8 al = *(const bf8 *)(sm.Jl + row * LD + kofs);
-          if (bi <= jlast[NBW - 1]) {  // every column block: accumulators in turn
-#pragma unroll
-            for (int j = 0; j < NBW; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < NBW; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < NBW; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
-          } else {
-#pragma unroll
-            for (int j = 0; j < NBW; ++j)
-              if (bi <= jlast[j]) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
-              }
-          }
-        }
+    for (int j = 0; j < NB; ++j) {
+      if (j < n0) {  // uniform
+        if (j + 1 < NB) load_b(j + 1);
+        if (j < n1) products<2>(acc[j], fa, fb[j & 1]);
+        else products<1>(acc[j], fa, fb[j & 1]);
       }
     }
   }
 }
 
 // Accumulators to Delta: lane holds rows 4g + v of each 16-row block, column
-// r16 of each column block.
-template <int MBW, int NBW, int BSTR>
-__device__ inline void store_acc(const FusedArgs &a, const Tile &t, const f4 (&acc)[MBW][NBW],
-                                 int bofs, int wc, int g, int r16) {
+// r16 of each column block.  Transposed (batch): columns of ldd >= 16 nlb
+// floats, a multiple of 32, so a lane's four rows are one 16-byte store and 64
+// bytes of a column go out together; blocks above the row's band (last_blk)
+// and column blocks whose models stop below are not written, nor read later.
+template <int WR, int NB>
+__device__ inline void store_acc(const FusedArgs &a, const Tile &t, const f4 (&acc)[NB][2],
+                                 const int (&njb)[2], int last_blk, int wr, int g, int r16) {
 #pragma unroll
-  for (int i = 0; i < MBW; ++i) {
-    const int blk = t.lb0 + bofs + BSTR * i;
-    if (blk > t.lb_last) break;
+  for (int i = 0; i < 2; ++i) {
+    const int blk = t.lb0 + wr + WR * i;
+    if (blk > last_blk) break;
 #pragma unroll
-    for (int j = 0; j < NBW; ++j) {
-      const int cc = t.c0 + wc * NBW * 16 + 16 * j + r16;
+    for (int j = 0; j < NB; ++j) {
+      const int cc = t.c0 + 16 * j + r16;
       if (cc >= t.ncol) continue;
+      if (a.dtrans) {
+        if (j < njb[i])
+          *(f4 *)(a.delta + t.dbase + (int64_t)cc * a.ldd + blk * 16 + 4 * g) = acc[j][i];
+        continue;
+      }
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = blk * 16 + 4 * g + v;
-        if (row < a.nl) {
-          const int64_t o = a.dtrans ? (int64_t)cc * a.nl + row : (int64_t)row * t.ncol + cc;
-          a.delta[t.dbase + o] = acc[i][j][v];
-        }
+        if (row < a.nl) a.delta[t.dbase + (int64_t)row * t.ncol + cc] = acc[j][i][v];
       }
     }
   }
 }
 
-// One workgroup per (k row, TM-row l tile, TN-column tile), WR x WC waves that
-// all take every role in turn: per active chunk each wave regenerates one
-// 32-row segment, the threads stage S, and after a barrier each wave
-// multiplies its row blocks wr, wr + WR, ... (interleaved, so that the waves
-// share a tile's partly filled upper blocks) by its column blocks; the next
-// chunk's inputs load meanwhile.
-template <int PREC, int WR, int WC, int MBW, int NBW>
-__global__ __launch_bounds__(64 * WR * WC) void fused_gemm_kernel(FusedArgs a, int tiles_m,
-                                                                  int tiles_n, int kcount) {
-  constexpr int NT = 64 * WR * WC;
-  constexpr int TM = WR * MBW * 16, TN = WC * NBW * 16;
-  static_assert(TM / 32 == WR * WC, "one 32-row segment per wave");
+// A workgroup multiplies a (k row, 32 WR-row l tile, 16 NB-column tile) at a
+// time, WR waves that all take every role in turn: per active chunk each wave
+// regenerates one 32-row segment, the threads stage S, and after a barrier
+// each wave multiplies its row blocks wr and wr + WR (interleaved, so that the
+// waves share a tile's partly filled upper blocks) by every column block (so
+// that they share any number of those evenly); the next chunk's inputs load
+// meanwhile.
+// The workgroups stay and take tiles from the lists until these are empty; the
+// list position of the next tile is fetched during the current one.
+template <int PREC, int WR, int NB, bool TINY>
+__global__ __launch_bounds__(64 * WR) void fused_gemm_kernel(FusedArgs a, int per_row,
+                                                                  int tiles_m, int kcount) {
+  constexpr int NT = 64 * WR, TM = 32 * WR, TN = 16 * NB;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int2 s_item;
 
-  Tile t;
-  if (!tile_of_block<TM, TN>(a, tiles_m, tiles_n, kcount, t)) return;  // uniform
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
   const int g = lane >> 4, r16 = lane & 15;
-  const int wr = w % WR, wc = w / WR;
   const Stage<PREC, TM, TN> sm(smem);
-  const Producer p = producer_of(a, t, t.tm * (TM / 32) + w);
-  const Chunks ch = active_chunks(a, t, lane);
-
-  f4 acc[MBW][NBW];
-#pragma unroll
-  for (int i = 0; i < MBW; ++i)
-#pragma unroll
-    for (int j = 0; j < NBW; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  int jlast[NBW];
-  column_limits(a, t, wc, jlast);
-
-  ChunkIn<SPieces<TN, NT>::SPT> in;
-  int c = next_chunk(ch.act0, ch.act1, 0);
-  if (c >= 0) load_chunk_in<TN, NT>(a, t, p, c, lane, tid, in);
-  while (c >= 0) {
-    const int top_tr = chunk_top(a, t, ch, c);
-    if (p.seg_ok && 32 * w <= top_tr) gen_segment(a, p, in, 32 * w, lane, sm);
-    store_s<PREC, TM, TN, NT>(in, tid, sm);
+  // S pieces that cross the end of tau: in the last chunk, by `tail` nodes
+  const int tail = TINY ? 0 : (int)(-a.ntau & 3), ctail = (int)(a.ntau / KB);
+  int from = 0;
+  int2 item = make_int2(0, -1);
+  if (tid == 0) item = first_tile<TN>(a, per_row, tiles_m, kcount, from);
+  for (;;) {
+    if (tid == 0) s_item = item;
     __syncthreads();
-    // the next active chunk's inputs are in flight while the matrix cores run
-    const int cn = next_chunk(ch.act0, ch.act1, c + 1);
-    if (cn >= 0) load_chunk_in<TN, NT>(a, t, p, cn, lane, tid, in);
-    // FP32: the wave's products go ahead of the other workgroup's segment
-    // generation on the SIMD (1 % on C4; nothing for split-BF16x3)
-    if constexpr (PREC == 1) __builtin_amdgcn_s_setprio(1);
-    mfma_chunk<PREC, TM, TN, MBW, NBW, WR>(acc, jlast, wr, wc, top_tr, g, r16, sm);
-    if constexpr (PREC == 1) __builtin_amdgcn_s_setprio(0);
-    __syncthreads();
-    c = cn;
+    const unsigned mk = __builtin_amdgcn_readfirstlane(s_item.x);
+    const int tn = __builtin_amdgcn_readfirstlane(s_item.y);
+    if (tn < 0) return;
+    const int ki = mk & 0xffff;
+    if (tid == 0) item = next_tile(a, per_row, kcount, from);
+    Tile t;
+    int need;
+    tile_at<TM, TN>(a, ki, mk >> 16, tn, lane, t, need);
+    const Producer p = producer_of(a, t, t.tm * WR + w);
+    const Chunks ch = active_chunks(a, t, lane);
+    int last_blk = t.lb_last;
+    if (a.dtrans) last_blk = min(last_blk, (a.rowtop[ki] - a.lmin) >> 4);
+
+    f4 acc[NB][2];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j][0] = acc[j][1] = f4{0.f, 0.f, 0.f, 0.f};
+    // column blocks whose models reach the wave's row blocks (the first njb[i]); the others'
+    // products are skipped
+    const int njb[2] = {(int)__popcll(__ballot(need >= w)), (int)__popcll(__ballot(need >= w + WR))};
+
+    ChunkIn<SPieces<TN, NT>::SPT> in;
+    int c = next_chunk(ch.act0, ch.act1, 0);
+    if (c >= 0) load_chunk_in<TN, NT, TINY>(a, t, p, c, lane, tid, in);
+    __syncthreads();  // s_item is read
+    while (c >= 0) {
+      const int top_tr = chunk_top(a, t, ch, c);
+      if (p.seg_ok && 32 * w <= top_tr) gen_segment(a, p, in, 32 * w, lane, sm);
+      store_s<PREC, TM, TN, NT>(in, t.nblk, c == ctail ? tail : 0, (int)a.ntau % KB / 4 * 4, tid,
+                               sm);
+      __syncthreads();
+      // the next active chunk's inputs are in flight while the matrix cores run
+      const int cn = next_chunk(ch.act0, ch.act1, c + 1);
+      // (after the last the same again: a load under a condition would be waited for here)
+      load_chunk_in<TN, NT, TINY>(a, t, p, cn >= 0 ? cn : c, lane, tid, in);
+      // FP32: the wave's products go ahead of the other workgroup's segment
+      // generation on the SIMD (1 % on C4; nothing for split-BF16x3)
+      if constexpr (PREC == 1) __builtin_amdgcn_s_setprio(1);
+      mfma_chunk<PREC, TM, TN, WR, NB>(acc, njb, w, top_tr, g, r16, sm);
+      if constexpr (PREC == 1) __builtin_amdgcn_s_setprio(0);
+      __syncthreads();
+      c = cn;
+    }
+    store_acc<WR, NB>(a, t, acc, njb, last_blk, w, g, r16);
   }
-  store_acc<MBW, NBW, WR>(a, t, acc, wr, wc, g, r16);
 }
 
-// Sets the large-LDS limit of a kernel once per device (a per-device function
-// attribute).
+// Per kernel and device: the large-LDS limit (a per-device function attribute) is set and the
+// number of workgroups that the device holds at once is read on the first launch.  Threads that
+// race here store the same values.
+struct Resident {
+  std::atomic<int> n[64] = {};
+};
+
 template <typename K>
-hipError_t allow_lds(K kern, size_t lds, bool (&done)[64]) {
+hipError_t resident_blocks(K kern, int threads, size_t lds, Resident &r, int &n) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (lds > 64 * 1024 && !done[dev]) {
+  n = r.n[dev].load();
+  if (n > 0) return hipSuccess;
+  if (lds > 64 * 1024) {
     e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds);
     if (e != hipSuccess) return e;
-    done[dev] = true;
   }
+  int cus = 0, per_cu = 0;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, threads, lds);
+  if (e != hipSuccess) return e;
+  n = (std::max(1, cus * per_cu) + 7) / 8 * 8;  // XCD = block index % 8
+  r.n[dev].store(n);
   return hipSuccess;
 }
 
-int64_t fused_grid(const FusedArgs &a, int kcount, int max_ncol, int tm, int tn, int &tiles_m,
-                   int &tiles_n) {
-  tiles_m = (a.nlb * 16 + tm - 1) / tm;
-  tiles_n = (max_ncol + tn - 1) / tn;
-  return 8 * (((int64_t)kcount + 7) / 8) * tiles_m * tiles_n;
-}
-
-template <int PREC, int WR, int WC, int MBW, int NBW>
+template <int PREC, int WR, int NB, bool TINY = false>
 hipError_t launch_fused_t(const FusedArgs &a, int kcount, int max_ncol, hipStream_t s) {
-  constexpr int TM = WR * MBW * 16, TN = WC * NBW * 16;
-  int tiles_m, tiles_n;
-  const int64_t grid = fused_grid(a, kcount, max_ncol, TM, TN, tiles_m, tiles_n);
-  if (grid > 0x7fffffff || grid < 1) return hipErrorInvalidValue;
+  constexpr int TM = 32 * WR, TN = 16 * NB;
+  const int tiles_m = (a.nlb * 16 + TM - 1) / TM, tiles_n = (max_ncol + TN - 1) / TN;
+  if (kcount < 1 || max_ncol < 1 || kcount > 65535 || tiles_m > 65535) return hipErrorInvalidValue;
   const size_t lds = LdsLayout<PREC>::bytes(TM, TN);
-  auto kern = fused_gemm_kernel<PREC, WR, WC, MBW, NBW>;
-  static bool done[64] = {};
-  hipError_t e = allow_lds(kern, lds, done);
+  auto kern = fused_gemm_kernel<PREC, WR, NB, TINY>;
+  static Resident resident;
+  int blocks = 0;
+  hipError_t e = resident_blocks(kern, 64 * WR, lds, resident, blocks);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WR * WC), lds, s, a, tiles_m,
-                     tiles_n, kcount);
+  const int64_t tiles = (int64_t)kcount * tiles_m * tiles_n;
+  FusedArgs arg = a;
+  if (!a.dtrans && !a.col_cnt && tiles <= blocks) {
+    // one tile each (60 k x 4 tiles: 17 us, and 23 us with the list kernel before it)
+    arg.queue = nullptr;
+    blocks = (int)tiles;
+  } else {
+    blocks = (int)std::min<int64_t>(blocks, (tiles + 7) / 8 * 8);
+    hipLaunchKernelGGL(tile_list_kernel, dim3(8), dim3(256), 0, s, a, TM, TN, tiles_m, tiles_n,
+                       kcount, blocks / 8);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * WR), lds, s, arg,
+                     tiles_m * tiles_n, tiles_m, kcount);
   return hipGetLastError();
 }
 
 template <int PREC>
 hipError_t launch_fused_p(const FusedArgs &a, int shape, int kcount, int max_ncol,
                           hipStream_t s) {
+  if (a.ntau < 4) return launch_fused_t<PREC, 4, 1, true>(a, kcount, max_ncol, s);
   switch (shape) {
-    case 0: return launch_fused_t<PREC, 4, 2, 4, 4>(a, kcount, max_ncol, s);  // 256 x 128
-    case 1: return launch_fused_t<PREC, 2, 2, 4, 4>(a, kcount, max_ncol, s);  // 128 x 128
-    case 2: return launch_fused_t<PREC, 2, 4, 8, 2>(a, kcount, max_ncol, s);  // 256 x 128
-    case 3: return launch_fused_t<PREC, 2, 4, 8, 4>(a, kcount, max_ncol, s);  // 256 x 256
-    case 4: return launch_fused_t<PREC, 8, 1, 2, 1>(a, kcount, max_ncol, s);  // 256 x 16
-    case 5: return launch_fused_t<PREC, 4, 1, 2, 1>(a, kcount, max_ncol, s);  // 128 x 16
+    case 0:
+    case 2: return launch_fused_t<PREC, 8, 8>(a, kcount, max_ncol, s);   // 256 x 128
+    case 1: return launch_fused_t<PREC, 4, 8>(a, kcount, max_ncol, s);   // 128 x 128
+    case 3: return launch_fused_t<PREC, 8, 16>(a, kcount, max_ncol, s);  // 256 x 256
+    case 4: return launch_fused_t<PREC, 8, 1>(a, kcount, max_ncol, s);   // 256 x 16
+    case 5: return launch_fused_t<PREC, 4, 1>(a, kcount, max_ncol, s);   // 128 x 16
+    case 6: return launch_fused_t<PREC, 4, 4>(a, kcount, max_ncol, s);   // 128 x 64
+    case 7: return launch_fused_t<PREC, 4, 2>(a, kcount, max_ncol, s);   // 128 x 32
     default: return hipErrorInvalidValue;
   }
 }
@@ -621,24 +761,36 @@ hipError_t launch_fused_p(const FusedArgs &a, int shape, int kcount, int max_nco
 
 FusedShape fused_shape_at(int i) {
   static const FusedShape shapes[kFusedShapeCount] = {
-      {256, 128}, {128, 128}, {256, 128}, {256, 256}, {256, 16}, {128, 16}};
+      {256, 128}, {128, 128}, {256, 128}, {256, 256}, {256, 16}, {128, 16},
+      {128, 64},  {128, 32}};
   return shapes[i];
 }
 
-size_t fused_seed_bytes_per_row(int nseg, int64_t ntp) {
-  return (size_t)ntp * (sizeof(int) + sizeof(double) + sizeof(double2) * (size_t)nseg) +
-         sizeof(int) * (size_t)(ntp / KB);
+// Tiles of a row at most: 128 rows by 16 columns is the smallest tile.
+static size_t row_tiles(int nseg, int max_ncol) {
+  return (size_t)((nseg + 3) / 4) * (size_t)((max_ncol + 15) / 16);
 }
 
-void fused_workspace_at(FusedArgs &a, void *ws, int kcount) {
+size_t fused_seed_bytes_per_row(int nseg, int64_t ntp, int max_ncol) {
+  return (size_t)ntp * (sizeof(int) + sizeof(double) + sizeof(double2) * (size_t)nseg) +
+         sizeof(int) * (size_t)(ntp / KB + 1) + sizeof(int2) * row_tiles(nseg, max_ncol);
+}
+
+void fused_workspace_at(FusedArgs &a, void *ws, int kcount, int max_ncol) {
   char *p = (char *)ws;
+  a.queue = (int *)p;
+  p += kFusedFixedBytes;
   a.seed = (double2 *)p;
   p += sizeof(double2) * (size_t)a.nseg * a.ntp * kcount;
   a.nix = (double *)p;
   p += sizeof(double) * (size_t)a.ntp * kcount;
+  a.items = (int2 *)p;
+  p += sizeof(int2) * row_tiles(a.nseg, max_ncol) * kcount;
   a.rtop = (int *)p;
   p += sizeof(int) * (size_t)a.ntp * kcount;
   a.cmax = (int *)p;
+  p += sizeof(int) * (size_t)(a.ntp / KB) * kcount;
+  a.rowtop = (int *)p;
 }
 
 hipError_t jseed_launch(const FusedArgs &a, int kcount, hipStream_t s) {
