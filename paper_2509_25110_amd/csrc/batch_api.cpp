@@ -321,8 +321,8 @@ int enqueue(los_batch *b, const SolveArgs &s, hipStream_t st) {
 // Fused pipeline: time the wide fused shapes (0, 1, 3) and, up to 64 columns, the
 // 32-column one (three of its workgroups fit a CU, but past 64 columns it generates
 // every J three times) on two representative chunks after building their seeds once;
-// keep the fastest total.  7 models, at most 21 columns: shape 7 1.90 ms against 1.97
-// (1) and 1.93 (0); 48 models, 96 columns: shape 1 34.7 ms against 35.1 (0) and 37.7 (7).
+// keep the fastest total.  7 models, at most 21 columns: shape 7 1.47 ms against 1.76
+// (1) and 1.95 (0); 48 models, 96 columns: shape 1 33.1 ms against 35.1 (0) and 35.3 (7).
 // LOS_BATCH_SHAPE pins a shape; LOS_BATCH_TUNE=0 keeps shape 0.
 int autotune_fused(los_batch *b, const SolveArgs &s, hipStream_t st) {
   const char *pin = std::getenv("LOS_BATCH_SHAPE");

@@ -49,8 +49,11 @@
 //                    half of each had 2 of 4 column blocks idle at 96 of 128 columns)
 //   40.4 -> 35.1     S and seed loads without tests or selects: the compiler had waited for them
 //                    before the products (vmcnt(0)) instead of after
-//   35.1 -> 33.9     a tile's column limits by one load; list heads on lines of their own
-// 7 models in split-BF16x3 (9 to 21 columns): 3.46 -> 1.51 ms.
+//   35.1 -> 33.3     a tile's column limits by one load; list heads on lines of their own
+//   33.3 -> 33.1     128-row tiles with 8 waves, 4 on a SIMD, half of the column blocks each
+// (the matrix cores busy 0.68 of the largest launch, 0.50 before).  7 models in split-BF16x3
+// (9 to 21 columns): 3.46 -> 1.50 -> 1.47 ms; 256 models: 170 -> 143 -> 136 ms in FP32,
+// 100 -> 74 -> 68 ms in split-BF16x3 (the last figure of each from the 8 waves).
 // Slower: S fragments from device memory straight to the lanes, no S in LDS (79 ms: each wave
 // loads them all, in half-used lines).
 #include <algorithm>
@@ -539,13 +542,13 @@ __device__ __forceinline__ void products(f4 (&acc)[2], const Frag<2> (&a)[2], co
 }
 
 // One chunk's products for one wave: its row blocks are wr and wr + WR of the
-// tile (those with data: 16 wr <= top_tr), every column block in turn; the two
+// tile (those with data: 16 wr <= top_tr), its column blocks in turn; the two
 // 32-node blocks of the chunk in increasing order.  Every accumulator sees its
 // terms in the same order whichever wave owns it.  A wave holds the fragments
 // of its rows and streams the columns', each read one block ahead.
-template <int PREC, int TM, int TN, int WR, int NB>
-__device__ inline void mfma_chunk(f4 (&acc)[NB][2], const int (&njb)[2], int wr, int top_tr, int g,
-                                  int r16, const Stage<PREC, TM, TN> &sm) {
+template <int PREC, int TM, int TN, int WR, int WC, int NB>
+__device__ inline void mfma_chunk(f4 (&acc)[NB][2], const int (&njb)[2], int wr, int wc,
+                                  int top_tr, int g, int r16, const Stage<PREC, TM, TN> &sm) {
   constexpr int LD = LdsLayout<PREC>::LD;
   const int n0 = 16 * wr <= top_tr ? njb[0] : 0;
   const int n1 = 16 * (wr + WR) <= top_tr ? njb[1] : 0;  // <= n0
@@ -561,7 +564,7 @@ __device__ inline void mfma_chunk(f4 (&acc)[NB][2], const int (&njb)[2], int wr,
       else fa[i].load(sm.Jh, sm.Jl, ofs);
     }
     auto load_b = [&](int j) {
-      const int ofs = 16 * j * LD + kofs;
+      const int ofs = 16 * (WC * j + wc) * LD + kofs;
       if constexpr (PREC == 1) fb[j & 1].load(sm.Sf, nullptr, ofs);
       else fb[j & 1].load(sm.Sh, sm.Sl, ofs);
     };
@@ -582,16 +585,17 @@ __device__ inline void mfma_chunk(f4 (&acc)[NB][2], const int (&njb)[2], int wr,
 // floats, a multiple of 32, so a lane's four rows are one 16-byte store and 64
 // bytes of a column go out together; blocks above the row's band (last_blk)
 // and column blocks whose models stop below are not written, nor read later.
-template <int WR, int NB>
+template <int WR, int WC, int NB>
 __device__ inline void store_acc(const FusedArgs &a, const Tile &t, const f4 (&acc)[NB][2],
-                                 const int (&njb)[2], int last_blk, int wr, int g, int r16) {
+                                 const int (&njb)[2], int last_blk, int wr, int wc, int g,
+                                 int r16) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int blk = t.lb0 + wr + WR * i;
     if (blk > last_blk) break;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int cc = t.c0 + 16 * j + r16;
+      const int cc = t.c0 + 16 * (WC * j + wc) + r16;
       if (cc >= t.ncol) continue;
       if (a.dtrans) {
         if (j < njb[i])
@@ -607,25 +611,25 @@ __device__ inline void store_acc(const FusedArgs &a, const Tile &t, const f4 (&a
   }
 }
 
-// A workgroup multiplies a (k row, 32 WR-row l tile, 16 NB-column tile) at a
-// time, WR waves that all take every role in turn: per active chunk each wave
-// regenerates one 32-row segment, the threads stage S, and after a barrier
-// each wave multiplies its row blocks wr and wr + WR (interleaved, so that the
-// waves share a tile's partly filled upper blocks) by every column block (so
-// that they share any number of those evenly); the next chunk's inputs load
-// meanwhile.
+// A workgroup multiplies a (k row, 32 WR-row l tile, 16 NB WC-column tile) at a time with WR x WC
+// waves: per active chunk the first WR waves regenerate one 32-row segment each, the threads
+// stage S, and after a barrier wave (wr, wc) multiplies its row blocks wr and wr + WR
+// (interleaved, so that the waves share a tile's partly filled upper blocks) by every WC-th
+// column block from wc on; the next chunk's inputs load meanwhile.  The waves of one wr are on
+// one SIMD (w and w + 4), so that any number of column blocks is shared evenly.
 // The workgroups stay and take tiles from the lists until these are empty; the
 // list position of the next tile is fetched during the current one.
-template <int PREC, int WR, int NB, bool TINY>
-__global__ __launch_bounds__(64 * WR) void fused_gemm_kernel(FusedArgs a, int per_row,
+template <int PREC, int WR, int WC, int NB, bool TINY>
+__global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kernel(FusedArgs a, int per_row,
                                                                   int tiles_m, int kcount) {
-  constexpr int NT = 64 * WR, TM = 32 * WR, TN = 16 * NB;
+  constexpr int NT = 64 * WR * WC, TM = 32 * WR, TN = 16 * NB * WC;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ int2 s_item;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
   const int g = lane >> 4, r16 = lane & 15;
+  const int wr = w % WR, wc = w / WR;
   const Stage<PREC, TM, TN> sm(smem);
   // S pieces that cross the end of tau: in the last chunk, by `tail` nodes
   const int tail = TINY ? 0 : (int)(-a.ntau & 3), ctail = (int)(a.ntau / KB);
@@ -643,7 +647,7 @@ __global__ __launch_bounds__(64 * WR) void fused_gemm_kernel(FusedArgs a, int pe
     Tile t;
     int need;
     tile_at<TM, TN>(a, ki, mk >> 16, tn, lane, t, need);
-    const Producer p = producer_of(a, t, t.tm * WR + w);
+    const Producer p = producer_of(a, t, t.tm * WR + wr);
     const Chunks ch = active_chunks(a, t, lane);
     int last_blk = t.lb_last;
     if (a.dtrans) last_blk = min(last_blk, (a.rowtop[ki] - a.lmin) >> 4);
@@ -653,7 +657,8 @@ __global__ __launch_bounds__(64 * WR) void fused_gemm_kernel(FusedArgs a, int pe
     for (int j = 0; j < NB; ++j) acc[j][0] = acc[j][1] = f4{0.f, 0.f, 0.f, 0.f};
     // column blocks whose models reach the wave's row blocks (the first njb[i]); the others'
     // products are skipped
-    const int njb[2] = {(int)__popcll(__ballot(need >= w)), (int)__popcll(__ballot(need >= w + WR))};
+    const int njb[2] = {((int)__popcll(__ballot(need >= wr)) + WC - 1 - wc) / WC,
+                        ((int)__popcll(__ballot(need >= wr + WR)) + WC - 1 - wc) / WC};
 
     ChunkIn<SPieces<TN, NT>::SPT> in;
     int c = next_chunk(ch.act0, ch.act1, 0);
@@ -661,7 +666,7 @@ __global__ __launch_bounds__(64 * WR) void fused_gemm_kernel(FusedArgs a, int pe
     __syncthreads();  // s_item is read
     while (c >= 0) {
       const int top_tr = chunk_top(a, t, ch, c);
-      if (p.seg_ok && 32 * w <= top_tr) gen_segment(a, p, in, 32 * w, lane, sm);
+      if (wc == 0 && p.seg_ok && 32 * wr <= top_tr) gen_segment(a, p, in, 32 * wr, lane, sm);
       store_s<PREC, TM, TN, NT>(in, t.nblk, c == ctail ? tail : 0, (int)a.ntau % KB / 4 * 4, tid,
                                sm);
       __syncthreads();
@@ -672,12 +677,12 @@ __global__ __launch_bounds__(64 * WR) void fused_gemm_kernel(FusedArgs a, int pe
       // FP32: the wave's products go ahead of the other workgroup's segment
       // generation on the SIMD (1 % on C4; nothing for split-BF16x3)
       if constexpr (PREC == 1) __builtin_amdgcn_s_setprio(1);
-      mfma_chunk<PREC, TM, TN, WR, NB>(acc, njb, w, top_tr, g, r16, sm);
+      mfma_chunk<PREC, TM, TN, WR, WC, NB>(acc, njb, wr, wc, top_tr, g, r16, sm);
       if constexpr (PREC == 1) __builtin_amdgcn_s_setprio(0);
       __syncthreads();
       c = cn;
     }
-    store_acc<WR, NB>(a, t, acc, njb, last_blk, w, g, r16);
+    store_acc<WR, WC, NB>(a, t, acc, njb, last_blk, wr, wc, g, r16);
   }
 }
 
@@ -711,16 +716,16 @@ hipError_t resident_blocks(K kern, int threads, size_t lds, Resident &r, int &n)
   return hipSuccess;
 }
 
-template <int PREC, int WR, int NB, bool TINY = false>
+template <int PREC, int WR, int WC, int NB, bool TINY = false>
 hipError_t launch_fused_t(const FusedArgs &a, int kcount, int max_ncol, hipStream_t s) {
-  constexpr int TM = 32 * WR, TN = 16 * NB;
+  constexpr int TM = 32 * WR, TN = 16 * NB * WC;
   const int tiles_m = (a.nlb * 16 + TM - 1) / TM, tiles_n = (max_ncol + TN - 1) / TN;
   if (kcount < 1 || max_ncol < 1 || kcount > 65535 || tiles_m > 65535) return hipErrorInvalidValue;
   const size_t lds = LdsLayout<PREC>::bytes(TM, TN);
-  auto kern = fused_gemm_kernel<PREC, WR, NB, TINY>;
+  auto kern = fused_gemm_kernel<PREC, WR, WC, NB, TINY>;
   static Resident resident;
   int blocks = 0;
-  hipError_t e = resident_blocks(kern, 64 * WR, lds, resident, blocks);
+  hipError_t e = resident_blocks(kern, 64 * WR * WC, lds, resident, blocks);
   if (e != hipSuccess) return e;
   const int64_t tiles = (int64_t)kcount * tiles_m * tiles_n;
   FusedArgs arg = a;
@@ -735,7 +740,7 @@ hipError_t launch_fused_t(const FusedArgs &a, int kcount, int max_ncol, hipStrea
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * WR), lds, s, arg,
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * WR * WC), lds, s, arg,
                      tiles_m * tiles_n, tiles_m, kcount);
   return hipGetLastError();
 }
@@ -743,16 +748,16 @@ hipError_t launch_fused_t(const FusedArgs &a, int kcount, int max_ncol, hipStrea
 template <int PREC>
 hipError_t launch_fused_p(const FusedArgs &a, int shape, int kcount, int max_ncol,
                           hipStream_t s) {
-  if (a.ntau < 4) return launch_fused_t<PREC, 4, 1, true>(a, kcount, max_ncol, s);
+  if (a.ntau < 4) return launch_fused_t<PREC, 4, 1, 1, true>(a, kcount, max_ncol, s);
   switch (shape) {
     case 0:
-    case 2: return launch_fused_t<PREC, 8, 8>(a, kcount, max_ncol, s);   // 256 x 128
-    case 1: return launch_fused_t<PREC, 4, 8>(a, kcount, max_ncol, s);   // 128 x 128
-    case 3: return launch_fused_t<PREC, 8, 16>(a, kcount, max_ncol, s);  // 256 x 256
-    case 4: return launch_fused_t<PREC, 8, 1>(a, kcount, max_ncol, s);   // 256 x 16
-    case 5: return launch_fused_t<PREC, 4, 1>(a, kcount, max_ncol, s);   // 128 x 16
-    case 6: return launch_fused_t<PREC, 4, 4>(a, kcount, max_ncol, s);   // 128 x 64
-    case 7: return launch_fused_t<PREC, 4, 2>(a, kcount, max_ncol, s);   // 128 x 32
+    case 2: return launch_fused_t<PREC, 8, 1, 8>(a, kcount, max_ncol, s);   // 256 x 128
+    case 1: return launch_fused_t<PREC, 4, 2, 4>(a, kcount, max_ncol, s);   // 128 x 128
+    case 3: return launch_fused_t<PREC, 8, 1, 16>(a, kcount, max_ncol, s);  // 256 x 256
+    case 4: return launch_fused_t<PREC, 8, 1, 1>(a, kcount, max_ncol, s);   // 256 x 16
+    case 5: return launch_fused_t<PREC, 4, 1, 1>(a, kcount, max_ncol, s);   // 128 x 16
+    case 6: return launch_fused_t<PREC, 4, 2, 2>(a, kcount, max_ncol, s);   // 128 x 64
+    case 7: return launch_fused_t<PREC, 4, 2, 1>(a, kcount, max_ncol, s);   // 128 x 32
     default: return hipErrorInvalidValue;
   }
 }
