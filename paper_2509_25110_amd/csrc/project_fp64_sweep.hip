@@ -37,12 +37,31 @@ size_t sweep_lds(int W, int64_t nodes, int nsrc) {
 // 565 nodes, 4 columns, 382 rows: 190 and 141 us; C2 (3000 nodes, one workgroup by LDS): 4,
 // 8, 12 waves 2.89, 2.10, 1.92 ms; 1777 nodes, 2 columns, 1501 rows: 4, 8, 12 waves 294,
 // 245, 280 us.
+//
+// Passes.  A row's nodes hold 26 bytes of LDS each for its whole time, so a long tau axis keeps
+// other rows off the CU and the waves of one row wait for each other (each for the block above,
+// all for the setup).  With rows enough for two rounds of as many 4-wave workgroups as the
+// registers allow (g), the nodes therefore go in as many passes as give every one of the g its
+// LDS; a pass adds to delta.  3 columns: C2 (2499 multipoles, 4000 k, 3000 nodes) 1776 us in one
+// pass of 12 waves, 1672 in two of 4 (sampled: 1350, 1198); 899, 3000, 4000: 915, 848 in three;
+// 249, 4000, 4096: 823, 736; but 899, 1200, 4000: 373, 445; 1499, 1000, 4000: 396, 668.  4
+// columns (two workgroups): 1499, 2000, 3000: 931, 876.  1 column: 1499, 3000, 4000: 811, 713
+// in four.  2 columns: 2499, 4000, 2500: 1115, 1004 in three.
 SweepShape project_sweep_shape(int nsrc, int64_t nk, int64_t ntau, int force_waves) {
   constexpr size_t kLds = 160 * 1024;
   const int wmax = sweep::max_waves(nsrc);
+  int64_t passes = 1;
+  if (force_waves <= 0 && nk >= 512 * (wmax / 4)) {
+    const int64_t fit = (int64_t)(kLds / (wmax / 4) - sweep_lds(4, 0, nsrc)) /
+                        (int64_t)sweep_lds(0, 64, nsrc) * 64;
+    if (ntau > fit) {
+      passes = (ntau + fit - 1) / fit;
+      force_waves = 4;
+    }
+  }
   // nodes per pass: all of them if 4 waves fit beside their LDS, else equal shares
   int64_t nodes = 0;
-  for (int64_t passes = 1;; ++passes) {
+  for (;; ++passes) {
     nodes = ((ntau + passes - 1) / passes + 63) / 64 * 64;
     if (nodes <= 64 * 128 && sweep_lds(4, nodes, nsrc) <= kLds) break;
   }
