@@ -128,18 +128,19 @@ int los_bessel_table(los_ctx *ctx, const double *x, int64_t nx, int32_t lmin, in
  * LOS_FP64: the j_l are generated on the fly in registers (never stored) and
  * the band where |j_l| < ~1e-21 of its peak is skipped.
  * LOS_FP32 / LOS_BF16X3: float sources and delta.  With at most 4 columns per k the
- * same FP64 sweep is the fastest way, so LOS_FP32 widens the sources as they are
- * read, forms every j_l and every sum in FP64 and rounds delta once (no workspace,
- * expected C_l error ~1e-7 relative).  LOS_BF16X3, and LOS_FP32 when LOS_MIXED_FUSED
- * or LOS_FUSED_SHAPE is set in the environment, run on the matrix cores (Eq. 2-3 as
- * the per-k matrix product Delta_k[l][s] = sum_n J_k[l][n] S[s][k][n],
- * J_k[l][n] = w_n j_l(k chi_n) computed in FP64 and rounded to FP32; expected C_l
- * error ~1e-6): a first kernel keeps only the FP64 recurrence state every 32
- * multipoles (a context workspace of at most LOS_JTAB_MIB MiB, environment, default
- * 4096, per chunk of k rows) and the product kernel regenerates each tile of J_k from
- * it in on-chip memory, multiplying in the given precision with FP32 accumulation;
- * LOS_MIXED_FUSED=0 selects whole FP32 tables in the workspace instead.  Those two
- * give the same values.
+ * same FP64 sweep is the fastest way for LOS_FP32: it widens the sources as they are
+ * read, forms every j_l and every sum in FP64 and rounds delta (once per pass over a
+ * part of a long tau axis; no workspace, expected C_l error ~1e-7 relative).
+ * LOS_BF16X3, and LOS_FP32 with few and long rows (at most 128 k from 640 multipoles
+ * on, 256 k from 2000 multipoles and 512 tau on) or when LOS_MIXED_FUSED or
+ * LOS_FUSED_SHAPE is set in the environment, run on the matrix cores (Eq. 2-3 as the
+ * per-k matrix product Delta_k[l][s] = sum_n J_k[l][n] S[s][k][n], J_k[l][n] =
+ * w_n j_l(k chi_n) computed in FP64 and rounded to FP32; expected C_l error ~1e-6): a
+ * first kernel keeps only the FP64 recurrence state every 32 multipoles (a context
+ * workspace of at most LOS_JTAB_MIB MiB, environment, default 4096, per chunk of k
+ * rows) and the product kernel regenerates each tile of J_k from it in on-chip memory,
+ * multiplying in the given precision with FP32 accumulation; LOS_MIXED_FUSED=0 selects
+ * whole FP32 tables in the workspace instead.  Those two give the same values.
  * Errors: LOS_ERR_OOM if the workspace cannot be allocated.
  */
 int los_project(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, int64_t ntau, double tau0,

@@ -350,15 +350,21 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
   // Mixed precision: float sources and delta.  A k row has at most 4 columns, of which the
   // matrix cores use 16 at a time and for which they need every Bessel value generated, rounded
   // and staged, so for LOS_FP32 the FP64 sweep takes these too (widening the sources as it
-  // reads them): C3 7.2 ms against 22.0 ms on the matrix cores, and no workspace.  LOS_BF16X3
-  // names the split product itself, whose values a batch at that precision has to match, and
-  // stays on the matrix cores (C3 22.4 ms).  LOS_MIXED_FUSED or LOS_FUSED_SHAPE in the
+  // reads them): C3 6.5 ms against 18 ms on the matrix cores, and no workspace.  A sweep's
+  // rows are whole workgroups, though, each a chain of blocks of multipoles: few and long rows
+  // go to the matrix cores, whose tiles cut them.  lmax 1000, 120 k, 1000 nodes: 78 us by the
+  // sweep, 71 on the matrix cores (250 k: 79, 113; lmax 300, 30 k: 33, 43); lmax 3000, 60 k, 150
+  // nodes: 108, 81; 250 k, 1000 nodes: 204, 178; 150 nodes: 107, 122; 500 k, 4000 nodes: 635, 688.
+  // LOS_BF16X3 names the split product itself, whose values a batch at that precision has to
+  // match, and stays on the matrix cores.  LOS_MIXED_FUSED or LOS_FUSED_SHAPE in the
   // environment select the matrix-core pipelines for both.
   const bool f32 = prec != LOS_FP64;
   if (f32 && kernel_mask != 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project: the E-mode kernel is FP64 only");
   const char *fz = std::getenv("LOS_MIXED_FUSED");
-  if (prec == LOS_BF16X3 || (f32 && (fz || std::getenv("LOS_FUSED_SHAPE")))) {
+  const int64_t nrows = (int64_t)lmax - lmin + 1;
+  const bool few_long = (nrows >= 640 && nk <= 128) || (nrows >= 2000 && nk <= 256 && ntau >= 512);
+  if (prec == LOS_BF16X3 || (f32 && (fz || few_long || std::getenv("LOS_FUSED_SHAPE")))) {
     const bool tables = fz && std::atoi(fz) == 0;
     int rc = tables ? project_mixed(ctx, lmin, lmax, nk, ntau, tau0, k, tau, w_tau,
                                     (const float *)S, nsrc, prec, (float *)delta,
