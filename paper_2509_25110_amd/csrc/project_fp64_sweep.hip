@@ -34,9 +34,9 @@ size_t sweep_lds(int W, int64_t nodes, int nsrc) {
 // number) is always within 4 % of the best, and the best is the largest
 //   W g / (1 + W / 10),  g = workgroups on a CU: what LDS and registers allow, at most nk / 256
 // e.g. 1751 nodes, 4 columns, 1253 rows: 4 waves 246 us (two workgroups), 8 waves 291 us (one);
-// 565 nodes, 4 columns, 382 rows: 190 and 141 us; C2 (3000 nodes, one workgroup by LDS): 4,
-// 8, 12 waves 2.89, 2.10, 1.92 ms; 1777 nodes, 2 columns, 1501 rows: 4, 8, 12 waves 294,
-// 245, 280 us.
+// 565 nodes, 4 columns, 382 rows: 190 and 141 us; C2 in one pass (3000 nodes, one workgroup
+// by LDS): 4, 8, 12 waves 2.86, 2.00, 1.78 ms; 1777 nodes, 2 columns, 1501 rows: 4, 8, 12
+// waves 327, 244, 281 us.
 //
 // Passes.  A row's nodes hold 26 bytes of LDS each for its whole time, so a long tau axis keeps
 // other rows off the CU and the waves of one row wait for each other (each for the block above,

@@ -90,9 +90,10 @@ __device__ __forceinline__ void sweep_slot(double (&acc)[B * NSRC], double &p1, 
 // Sampled multipoles: C sampled rows of a block, off[r] rows below its top (uniform).  The
 // recurrence alone runs through the block (2 FP64 instructions a row instead of 2 + NSRC), its
 // 16 values stay in registers and the sampled ones are picked by a uniform index; no branch.
-// C2 at 91 multipoles: 1.87 -> 1.46 ms a pass against sweeping every block densely.  (A test per row in sweep_slot costs the compiler 300 spilled registers; runs from sample to
-// sample with loops in between were no faster than the dense sweep: 80 scalar instructions
-// and 20 branches a slot.)
+// C2 at 91 multipoles, one pass: 1.87 -> 1.46 ms against sweeping every block densely.  (A test
+// per row in sweep_slot costs the compiler 300 spilled registers; runs from sample to sample
+// with loops in between were no faster than the dense sweep: 80 scalar instructions and 20
+// branches a slot.)
 template <int NSRC, int C, int N>
 __device__ __forceinline__ void sampled_slot(double (&acc)[N], double &p1,
                                              double &p0, double ix, const double (&sv)[NSRC],
@@ -125,9 +126,9 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // NV values summed over a wave's lanes (16 NSRC for a whole block).  Two exchange steps
-// (lanes 32 and 16 apart) leave NV / 4 values per lane, summed over 4 lanes; these go through the wave's LDS
-// stage, [16][NV / H + 1] (the pad keeps both its accesses free of bank conflicts), in H
-// rounds.  f(e, total) is called by the lane that holds the total of value e.  Two rounds
+// (lanes 32 and 16 apart) leave NV / 4 values per lane, summed over 4 lanes; these go through
+// the wave's LDS stage, [16][NV / H + 1] (the pad keeps both its accesses free of bank
+// conflicts), in H rounds.  f(e, total) is called by the lane that holds the total of value e.  Two rounds
 // (from 2 columns on) halve the stage, which decides how many waves fit a CU's LDS.
 constexpr int reduce_rounds(int nv) { return nv <= 16 ? 1 : 2; }
 constexpr int stage_doubles(int nsrc) { return 16 * (B * nsrc / reduce_rounds(B * nsrc) + 1); }
