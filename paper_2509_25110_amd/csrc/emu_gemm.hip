@@ -300,9 +300,9 @@ struct Recon {
 // Bound by the FP64 exp and sinh (VALU) beside the matrix cores: 4096 rows x 4999 multipoles
 // x 4 members take 1.25 ms (1.66 ms with the library's exp and sinh; three waves a SIMD,
 // 1.38 ms with two).
-template <int MEM, int WM, int WN>
+template <int MEM, int WM, int WN, int NB, int KT>
 __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
-  constexpr int TM = 16 * WM, TN = 32 * WN, KT = 32, LD = KT + 4;
+  constexpr int TM = 16 * WM, TN = 16 * NB * WN, LD = KT + 4;
   typedef Operand<true, MEM * TM, KT, 256> OA;
   typedef Operand<true, TN, KT, 256> OB;
   __shared__ __attribute__((aligned(16))) float As[OA::size];
@@ -318,18 +318,18 @@ __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
   for (int ct = 0; ct < a.ctiles; ++ct) {
     const int64_t col0 = ((int64_t)blockIdx.y * a.ctiles + ct) * TN;
     if (col0 >= a.nl) break;  // uniform
-    double keep[2][4];  // TT mean, then the TE scale
+    double keep[NB][4];  // TT mean, then the TE scale
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) keep[j][v] = 0.0;
 #pragma unroll 1
     for (int sp = 0; sp < 4; ++sp) {
-      f4 acc[MEM][2];
+      f4 acc[MEM][NB];
 #pragma unroll
       for (int e = 0; e < MEM; ++e)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[e][j] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NB; ++j) acc[e][j] = f4{0.f, 0.f, 0.f, 0.f};
       f4 ra[OA::F], rb[OB::F];
       auto load = [&](int k0) {
         // row e TM + i of the A tile is row row0 + i of member e
@@ -359,14 +359,14 @@ __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
         if (k0 + KT < a.nc) load(k0 + KT);
         const int kn = a.nc - k0 < KT ? a.nc - k0 : KT;
         for (int kk = 0; kk < kn; kk += 4) {
-          float b[2];
+          float b[NB];
 #pragma unroll
-          for (int j = 0; j < 2; ++j) b[j] = Bs[(32 * wn + 16 * j + r16) * LD + kk + kq];
+          for (int j = 0; j < NB; ++j) b[j] = Bs[(16 * (NB * wn + j) + r16) * LD + kk + kq];
 #pragma unroll
           for (int e = 0; e < MEM; ++e) {
             const float x = As[(e * TM + 16 * wm + r16) * LD + kk + kq];
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NB; ++j)
               acc[e][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, b[j], acc[e][j], 0, 0, 0);
           }
         }
@@ -376,8 +376,8 @@ __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
         constexpr bool TE = decltype(te)::value;
         const coef_ptr ck = inv_fact();
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int64_t l = col0 + 32 * wn + 16 * j + r16;
+        for (int j = 0; j < NB; ++j) {
+          const int64_t l = col0 + 16 * (NB * wn + j) + r16;
           const bool inl = l < a.nl;
           const float mu = inl ? a.mean[(int64_t)sp * a.nl + l] : 0.f;
           const double tl = TE && inl ? a.t[l] : 0.0;
@@ -433,17 +433,18 @@ __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
 
 template <int MEM>
 hipError_t launch_recon(Recon a, hipStream_t s) {
-  // few rows: 16 rows by 128 multipoles a workgroup; else 32 by 64, and several column
-  // tiles per workgroup (fewer atomics) as long as every CU has four workgroups
+  // few rows: 16 rows by 64 multipoles a workgroup (3 rows, 2499 multipoles: call 97.7 us, by 128
+  // 104.2); else 32 by 64, and several column tiles per workgroup (fewer atomics) as long as
+  // every CU has four workgroups
   if (a.n <= 16) {
     a.ctiles = 1;
-    hipLaunchKernelGGL((reconstruct_kernel<MEM, 1, 4>), dim3(1, (unsigned)((a.nl + 127) / 128)),
+    hipLaunchKernelGGL((reconstruct_kernel<MEM, 1, 4, 1, 32>), dim3(1, (unsigned)((a.nl + 63) / 64)),
                        dim3(256), 0, s, a);
     return hipGetLastError();
   }
   const int64_t rt = (a.n + 31) / 32, cts = (a.nl + 63) / 64;
   a.ctiles = (int)std::min<int64_t>(16, std::max<int64_t>(1, rt * cts / 1024));
-  hipLaunchKernelGGL((reconstruct_kernel<MEM, 2, 2>),
+  hipLaunchKernelGGL((reconstruct_kernel<MEM, 2, 2, 2, 32>),
                      dim3((unsigned)rt, (unsigned)((cts + a.ctiles - 1) / a.ctiles)), dim3(256), 0, s,
                      a);
   return hipGetLastError();
