@@ -34,8 +34,9 @@ struct ProjectArgs {
   const int32_t *lsel = nullptr;
   const uint32_t *bmask = nullptr;
   int nls = 0;
-  // Sweep kernel: this launch's tau nodes n0 .. n0 + ncnt - 1 (set per pass by the
-  // launcher); accumulate: add to the delta of the passes before.
+  // Sweep kernel: this launch's k rows, kend - 1 and down, and tau nodes n0 .. n0 + ncnt - 1
+  // (set per launch by the launcher); accumulate: add to the delta of the passes before.
+  int64_t kend = 0;
   int n0 = 0, ncnt = 0;
   bool accumulate = false;
 };

@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(64 * max_waves(NSRC)) project_fp64_sweep_kerne
 
   const int W = blockDim.x >> 6;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int64_t ki = a.nk - 1 - (int64_t)blockIdx.x;  // large k (most work) first
+  const int64_t ki = a.kend - 1 - (int64_t)blockIdx.x;  // large k (most work) first
   const int lmin = a.lmin, lmax = a.lmax;
   const int nblk = (a.nl + B - 1) / B;
   const int n0 = a.n0, ncnt = a.ncnt;  // this pass's nodes

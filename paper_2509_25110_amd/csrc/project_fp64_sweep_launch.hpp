@@ -17,13 +17,19 @@ hipError_t launch_t(const ProjectArgs &a, const SweepShape &sh, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   ProjectArgs b = a;
+  // A launch counts its threads in 32 bits and takes a larger grid without an error, modulo
+  // 2^32: from 2^26 / waves rows on (2^24 with 4 waves) the rows go in several launches.
+  const int64_t rows = ((int64_t)1 << 26) / sh.waves - 1;
   for (int64_t n0 = 0; n0 < a.ntau; n0 += sh.nodes) {
     b.n0 = (int)n0;
     b.ncnt = (int)(a.ntau - n0 < sh.nodes ? a.ntau - n0 : sh.nodes);
     b.accumulate = n0 > 0;
-    hipLaunchKernelGGL(kern, dim3((unsigned)b.nk), dim3(64 * sh.waves), sh.lds, s, b);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    for (b.kend = a.nk; b.kend > 0; b.kend -= rows) {
+      const int64_t cnt = b.kend < rows ? b.kend : rows;
+      hipLaunchKernelGGL(kern, dim3((unsigned)cnt), dim3(64 * sh.waves), sh.lds, s, b);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }
