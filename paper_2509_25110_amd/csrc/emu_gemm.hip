@@ -233,48 +233,66 @@ hipError_t launch_gemm(const GemmF32 &g, hipStream_t s) {
 
 // ------------------------------------------------ reconstruction and ensemble
 
-// 1 / k!
-__constant__ const double kInvFact[18] = {
-    1.0, 1.0, 0.5, 0.16666666666666666, 0.041666666666666664, 0.008333333333333333,
-    0.001388888888888889, 0.0001984126984126984, 2.48015873015873e-05, 2.7557319223985893e-06,
-    2.755731922398589e-07, 2.505210838544172e-08, 2.08767569878681e-09, 1.6059043836821613e-10,
-    1.1470745597729725e-11, 7.647163731819816e-13, 4.779477332387385e-14, 2.8114572543455206e-15};
+// exp: (e^r - 1 - r) / r^2 on |r| <= ln 2 / 2, degree 10 (gen_exp.py); then sinh: 1 / k! for
+// k = 3, 5, .. 17.
+__constant__ const double kExpSinh[19] = {
+    0.5, 0.16666666666666671, 0.041666666666666671, 0.0083333333333261411, 0.0013888888888883752,
+    0.00019841269874800683, 2.4801587325533502e-05, 2.75572554255029e-06, 2.7557273661174726e-07,
+    2.5105206475334834e-08, 2.091467944897855e-09,
+    0.16666666666666666, 0.008333333333333333, 0.0001984126984126984, 2.7557319223985893e-06,
+    2.505210838544172e-08, 1.6059043836821613e-10, 7.647163731819816e-13, 2.8114572543455206e-15};
 
 // Uniform coefficients by scalar loads: as literals they would sit in vector registers.
 typedef const __attribute__((address_space(4))) double *coef_ptr;
-__device__ inline coef_ptr inv_fact() {
-  coef_ptr p = (coef_ptr)(const double *)kInvFact;
+__device__ inline coef_ptr exp_sinh_coef() {
+  coef_ptr p = (coef_ptr)(const double *)kExpSinh;
   asm volatile("" : "+s"(p));  // an address the compiler does not look through
   return p;
 }
 
-// e^y: y = n ln 2 + r, |r| <= ln 2 / 2 (ln 2 in two parts), Taylor's polynomial of degree 13
-// (next term below 5e-18), scaled by 2^n; times 2^shift.  Below 1 unit in the last place;
-// overflows to inf, underflows to 0, NaN stays NaN.  About half the instructions of the
-// library's exp.
-__device__ __forceinline__ double exp_f64(double y, coef_ptr c, int shift = 0) {
-  y = y > 800.0 ? 800.0 : y;
-  y = y < -800.0 ? -800.0 : y;
-  const double n = rint(y * 1.4426950408889634);
-  double r = fma(-n, 0x1.62e42fefa3800p-1, y);
-  r = fma(-n, 0x1.ef35793c76730p-45, r);
-  double p = c[13];
+// e^y = (hi + lo) 2^n, hi = 1 + r rounded, |lo| < 0.07: y = n ln 2 + r, |r| <= ln 2 / 2, with ln 2
+// as the sum of its first 42 bits (n times them is exact) and the next 53; r's own rounding
+// error and the polynomial's terms, from r^2 on, go to lo.  Past +-800 e^y is inf or 0 as there.
+__device__ __forceinline__ int exp_parts(float yf, coef_ptr c, double &hi, double &lo) {
+  yf = yf > 800.f ? 800.f : yf;
+  yf = yf < -800.f ? -800.f : yf;
+  const double y = (double)yf, n = rint(y * 1.4426950408889634);
+  const double r0 = fma(-n, 0x1.62e42fefa3800p-1, y);
+  const double r = fma(-n, 0x1.ef35793c76730p-45, r0);
+  const double rl = fma(-n, 0x1.ef35793c76730p-45, r0 - r);
+  double q = c[10];
 #pragma unroll
-  for (int k = 12; k >= 0; --k) p = fma(p, r, c[k]);
-  return ldexp(p, (int)n + shift);
+  for (int k = 9; k >= 0; --k) q = fma(q, r, c[k]);
+  hi = 1.0 + r;
+  lo = ((1.0 - hi) + r) + fma(r * r, q, rl);
+  return (int)n;
 }
 
-// sinh y: (e^|y| - e^-|y|) / 2 from |y| = 1 on, Taylor's polynomial below (next term below
-// 9e-18 of y): within 2 units in the last place.  The library's sinh forms e^y in
-// double-double, 4 times the instructions.
-__device__ __forceinline__ double sinh_f64(double y, coef_ptr c) {
-  const double a = fabs(y), h = exp_f64(a, c, -1);  // e^|y| / 2, finite as long as sinh is
-  const double big = h - 0.25 / h;
-  const double y2 = y * y;
-  double p = c[17];
+// e^y: at most 0.64 units in the last place from it (the library's exp: 0.864), over 5.3 million
+// arguments against 113 bits; overflows to inf, underflows to 0, NaN stays NaN.  About 2/3 of the
+// library's instructions.
+__device__ __forceinline__ double exp_f64(float y, coef_ptr c) {
+  double hi, lo;
+  const int n = exp_parts(y, c, hi, lo);
+  return ldexp(hi + lo, n);
+}
+
+// sinh y: (e^|y| - e^-|y|) / 2 from |y| = 1 on, Taylor's polynomial below (next term below 9e-18
+// of y; y^2 is exact, y having 24 bits).  At most 0.77 units in the last place (the library's,
+// which forms e^y in double-double with 4 times the instructions: 0.858), as above.
+__device__ __forceinline__ double sinh_f64(float yf, coef_ptr c) {
+  double hi, lo;
+  const int n = exp_parts(fabsf(yf), c, hi, lo);
+  const double s = hi + lo;  // in [0.7, 1.42]: 1 / s by Newton's steps from an estimate
+  double g = __builtin_amdgcn_rcp(s);
+  g = fma(fma(-s, g, 1.0), g, g);
+  g = fma(fma(-s, g, 1.0), g, g);
+  const double big = ldexp(hi + (lo - ldexp(g, -2 * n)), n - 1);
+  const double y = (double)yf, y2 = y * y;
+  double p = c[18];
 #pragma unroll
-  for (int k = 15; k >= 1; k -= 2) p = fma(p, y2, c[k]);
-  return a < 1.0 ? y * p : copysign(big, y);
+  for (int k = 17; k >= 11; --k) p = fma(p, y2, c[k]);
+  return fabsf(yf) < 1.f ? fma(y * y2, p, y) : copysign(big, y);
 }
 
 struct Recon {
@@ -298,8 +316,9 @@ struct Recon {
 // twice, and exp and sinh were taken twice.  The division by the scale is monotone, so the
 // largest |C_e - cl| is divided once.
 // Bound by the FP64 exp and sinh (VALU) beside the matrix cores: 4096 rows x 4999 multipoles
-// x 4 members take 1.25 ms (1.66 ms with the library's exp and sinh; three waves a SIMD,
-// 1.38 ms with two).
+// x 4 members take 1.27 ms (1.66 ms with the library's exp and sinh; 1.22 ms with exp and sinh
+// that were less accurate than these), three waves a SIMD at the price of 24 spilled registers
+// (96 bytes of scratch a lane); two waves were 0.13 ms slower.
 template <int MEM, int WM, int WN, int NB, int KT>
 __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
   constexpr int TM = 16 * WM, TN = 16 * NB * WN, LD = KT + 4;
@@ -374,7 +393,7 @@ __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
       // the spectrum's values: TE as t sinh(y), the others as exp(y)
       auto finish = [&](auto te) {
         constexpr bool TE = decltype(te)::value;
-        const coef_ptr ck = inv_fact();
+        const coef_ptr ck = exp_sinh_coef();
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
           const int64_t l = col0 + 16 * (NB * wn + j) + r16;
@@ -388,7 +407,7 @@ __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {
             double c[MEM], mean = 0.0;
 #pragma unroll
             for (int e = 0; e < MEM; ++e) {
-              const double y = (double)(acc[e][j][v] + mu);
+              const float y = acc[e][j][v] + mu;
               c[e] = TE ? tl * sinh_f64(y, ck) : exp_f64(y, ck);
               mean += c[e];
             }
