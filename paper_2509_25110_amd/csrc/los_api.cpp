@@ -192,7 +192,7 @@ int project_mixed_fused(los_ctx *ctx, int lmin, int lmax, int64_t nk, int64_t nt
   fa.ncol = nsrc;
   fa.dtrans = 0;
   fa.delta = delta;
-  const size_t per_k = los::fused_seed_bytes_per_row(fa.nseg, fa.ntp, nsrc);
+  const size_t per_k = los::fused_seed_bytes_per_row(fa.nseg, fa.ntp, 0);
   const int64_t kc = jtab_chunk(nk, per_k);
   void *ws = nullptr;
   int rc = ws_reserve(ctx, WS_JTAB, los::kFusedFixedBytes + per_k * (size_t)kc, &ws);
@@ -204,7 +204,7 @@ int project_mixed_fused(los_ctx *ctx, int lmin, int lmax, int64_t nk, int64_t nt
   for (int64_t k0 = 0; k0 < nk; k0 += kc) {
     const int cnt = (int)(nk - k0 < kc ? nk - k0 : kc);
     fa.k0 = k0;
-    los::fused_workspace_at(fa, ws, cnt, nsrc);
+    los::fused_workspace_at(fa, ws, cnt, 0);
     hipError_t e = los::jseed_launch(fa, cnt, stream);
     if (e != hipSuccess) return hip_fail(e, "los_project: Bessel seed launch");
     e = los::fused_gemm_launch(fa, prec, shape, cnt, nsrc, stream);

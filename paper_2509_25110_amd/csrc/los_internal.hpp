@@ -160,7 +160,8 @@ struct FusedShape {
 // 7 128x32.
 constexpr int kFusedShapeCount = 8;
 FusedShape fused_shape_at(int i);
-// Workspace: kFusedFixedBytes + rows * fused_seed_bytes_per_row (rows of at most max_ncol columns).
+// Workspace: kFusedFixedBytes + rows * fused_seed_bytes_per_row (dtrans: rows of at most max_ncol
+// columns, for the lists; else max_ncol = 0).
 constexpr size_t kFusedFixedBytes = 2048;
 size_t fused_seed_bytes_per_row(int nseg, int64_t ntp, int max_ncol);
 void fused_workspace_at(FusedArgs &a, void *ws, int kcount, int max_ncol);

@@ -10,24 +10,21 @@
 //   and R per node and the largest R of every chunk of 64 nodes.  Nothing of
 //   J itself is stored.
 //
-// tile_list_kernel: the (k row, TM-row l tile, TN-column tile) items that hold
-//   data, as one list per XCD.
+// tile_list_kernel (batches of many tiles): the (k row, TM-row l tile, TN-column
+//   tile) items that hold data, as one list per XCD.
 //
-// fused_gemm_kernel (as many workgroups as the device holds, each taking tiles
-//   from the lists): the tau axis advances in chunks of 64 nodes, visiting only the
-//   chunks whose largest R reaches the tile (two ballots over the chunk
-//   table), and the sources, seeds and R of the next such chunk are loaded
-//   while the matrix cores work on the current one.  Per chunk every
-//   wave regenerates one 32-row segment of the l tile for the 64 nodes from
-//   the seeds (FP64 recurrence in registers, one lane per node, rounded to
-//   FP32 -- or split into bf16 hi/lo -- as it is written to LDS), the S
-//   columns of the tile are staged in LDS, and the matrix cores multiply the
-//   two.  The recurrence runs with the same coefficient cadence as the
-//   Bessel-table kernel (coefficient (2l+1)/x formed exactly at the rows
-//   16b + 15 and 16b + 7 above lmin, stepped by -2/x in between), so the
-//   generated values are those of the table, and the products are
-//   accumulated in the same order as the table-based kernels (32-node blocks
-//   in increasing order; within a block the same fragment layout).
+// fused_gemm_kernel (as many workgroups as the device holds, each taking tiles from the lists, or
+//   one per possible tile): the tau axis advances in chunks of 64 nodes, visiting only the
+//   chunks whose largest R reaches the tile (two ballots over the chunk table), and the sources,
+//   seeds and R of the next such chunk are loaded while the matrix cores work on the current
+//   one.  Per chunk every wave regenerates one 32-row segment of the l tile for the 64 nodes
+//   from the seeds (FP64 recurrence in registers, one lane per node, rounded to FP32 -- or split
+//   into bf16 hi/lo -- as it is written to LDS), the S columns of the tile are staged in LDS,
+//   and the matrix cores multiply the two.  The recurrence runs with the same coefficient
+//   cadence as the Bessel-table kernel (coefficient (2l+1)/x formed exactly at the rows 16b + 15
+//   and 16b + 7 above lmin, stepped by -2/x in between), so the generated values are those of
+//   the table, and the products are accumulated in the same order as the table-based kernels
+//   (32-node blocks in increasing order; within a block the same fragment layout).
 //
 // Data per chunk row kc (workspace):
 //   rtop[kc * ntp + n]                 R (absolute l) or -1 (no row in band)
@@ -36,7 +33,7 @@
 //                                      written for segments with lmin + 32 s <= R
 //   cmax[kc * (ntp / 64) + c]          max of rtop over nodes 64 c .. 64 c + 63
 //   rowtop[kc]                         max of the row's cmax
-//   items, queue                       the tiles with data, per XCD, and the lists' heads
+//   items, queue                       with lists: the tiles with data, per XCD, and the heads
 // ntp = nodes padded to a multiple of 64 (at most 8192, so at most 128 chunks).
 //
 // What bounds it (48 models, 3 sources, l <= 5000, 8000 k, 3000 nodes; 84 to 102 columns a row):
@@ -158,9 +155,8 @@ __device__ inline int64_t list_base(int x, int kcount) {
 // a row the l tiles of one column tile follow each other (they read the same S columns, kept in
 // that XCD's L2).  Also the row's band top, and the lists' heads and lengths for the product's
 // workgroups.  Launching a workgroup per possible tile instead left most of the chip idle where
-// few tiles hold data: the dispatcher deals workgroups to the shader engines in turn, and with an
-// even number of tiles a row the full ones all went to the same engines (48 models, 3 sources,
-// l <= 5000: the 900 smallest k, one full tile each, 1.38 ms; now 0.56 ms).
+// few tiles hold data (48 models, 3 sources, l <= 5000: the 900 smallest k, one full tile each,
+// 1.38 ms; now 0.56 ms).  Transposed products only: untransposed, every tile has zeros to write.
 __global__ __launch_bounds__(256) void tile_list_kernel(FusedArgs a, int tm, int tn, int tiles_m,
                                                         int tiles_n, int kcount, int places) {
   __shared__ int s_sum[4];
@@ -177,8 +173,6 @@ __global__ __launch_bounds__(256) void tile_list_kernel(FusedArgs a, int tm, int
       const int *cm = a.cmax + (int64_t)ki * nch;
       for (int c = 0; c < nch; ++c) top = max(top, cm[c]);
       a.rowtop[ki] = top;
-      // untransposed: every tile, those above the band write the zeros there
-      if (!a.dtrans) top = a.lmin + 16 * a.nlb - 1;
       ncol = a.col_cnt ? a.col_cnt[a.k0 + ki] : a.ncol;
       if (top >= a.lmin)
         for (int c0 = 0; c0 < ncol; c0 += tn)
@@ -291,20 +285,26 @@ __device__ inline void tile_at(const FusedArgs &a, int ki, int tm, int tn, int l
 // place s of list x.  The rest of list x, from place gridDim.x / 8 on, and then of the other
 // lists, are taken as they come.  A list's head is read before it is raised, and each has a cache
 // line of its own: some hundred workgroups raising one line's heads at the end made 300 us.
-// Without lists (queue nullptr: a launch of at most one tile per workgroup whose empty tiles have
-// zeros to write) workgroup L has tile L.
-template <int TN>
+// Without lists (queue nullptr) every possible tile is a workgroup, dealt to the XCDs as the lists
+// are; those past the row's columns or their l_max have nothing to do.  An XCD deals its workgroups
+// to 4 shader engines in turn: with an even number of tiles a row the same ones got every row's
+// full tiles, unless the order turns with the row (l <= 2500, 4000 k, 3000 nodes, 3 sources: 3.36 ->
+// 2.86 ms, l <= 1000, 3000 k, 500 nodes: 490 -> 278 us).
+template <int TM, int TN>
 __device__ inline int2 first_tile(const FusedArgs &a, int per_row, int tiles_m, int kcount,
                                   int &from) {
+  const int x = blockIdx.x & 7, s = blockIdx.x >> 3;
   if (!a.queue) {
     from = 8;
-    const int kr = blockIdx.x / per_row, u = blockIdx.x % per_row;
-    const int tn = u / tiles_m;
-    if (kr >= kcount || tn * TN >= a.ncol)
+    const int row = s / per_row, pos = (s + (per_row & 1 ? 0 : row >> 1)) % per_row;
+    const int ki = kcount - 1 - x - 8 * row, u = pos % tiles_m, tn = pos / tiles_m;
+    if (ki < 0) return make_int2(0, -1);
+    const int64_t r = a.k0 + ki;
+    if (tn * TN >= (a.col_cnt ? a.col_cnt[r] : a.ncol) ||
+        u * (TM / 16) > last_block(a, r, tn * TN))
       return make_int2(0, -1);
-    return make_int2((int)((unsigned)(u % tiles_m) << 16 | kr), tn);
+    return make_int2((int)((unsigned)u << 16 | ki), tn);
   }
-  const int x = blockIdx.x & 7, s = blockIdx.x >> 3;
   if (s < a.queue[kQueueStride * x + 1]) return a.items[list_base(x, kcount) * per_row + s];
   from = 8;  // list x has no more than one tile for each of its workgroups
   return make_int2(0, -1);
@@ -617,8 +617,8 @@ __device__ inline void store_acc(const FusedArgs &a, const Tile &t, const f4 (&a
 // (interleaved, so that the waves share a tile's partly filled upper blocks) by every WC-th
 // column block from wc on; the next chunk's inputs load meanwhile.  The waves of one wr are on
 // one SIMD (w and w + 4), so that any number of column blocks is shared evenly.
-// The workgroups stay and take tiles from the lists until these are empty; the
-// list position of the next tile is fetched during the current one.
+// With lists the workgroups stay and take tiles until these are empty; the list
+// position of the next tile is fetched during the current one.
 template <int PREC, int WR, int WC, int NB, bool TINY>
 __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kernel(FusedArgs a, int per_row,
                                                                   int tiles_m, int kcount) {
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kern
   const int tail = TINY ? 0 : (int)(-a.ntau & 3), ctail = (int)(a.ntau / KB);
   int from = 0;
   int2 item = make_int2(0, -1);
-  if (tid == 0) item = first_tile<TN>(a, per_row, tiles_m, kcount, from);
+  if (tid == 0) item = first_tile<TM, TN>(a, per_row, tiles_m, kcount, from);
   for (;;) {
     if (tid == 0) s_item = item;
     __syncthreads();
@@ -650,7 +650,16 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kern
     const Producer p = producer_of(a, t, t.tm * WR + wr);
     const Chunks ch = active_chunks(a, t, lane);
     int last_blk = t.lb_last;
-    if (a.dtrans) last_blk = min(last_blk, (a.rowtop[ki] - a.lmin) >> 4);
+    if (a.dtrans) {
+      int top;
+      if (a.queue) {
+        top = a.rowtop[ki];
+      } else {  // no list kernel has left it: the row's first tile does
+        top = wave_max_int(max(ch.cm0, ch.cm1));
+        if (t.tm == 0 && tn == 0 && tid == 0) a.rowtop[ki] = top;
+      }
+      last_blk = min(last_blk, (top - a.lmin) >> 4);
+    }
 
     f4 acc[NB][2];
 #pragma unroll
@@ -683,6 +692,7 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kern
       c = cn;
     }
     store_acc<WR, WC, NB>(a, t, acc, njb, last_blk, wr, wc, g, r16);
+    if (!a.queue) return;
   }
 }
 
@@ -729,16 +739,23 @@ hipError_t launch_fused_t(const FusedArgs &a, int kcount, int max_ncol, hipStrea
   if (e != hipSuccess) return e;
   const int64_t tiles = (int64_t)kcount * tiles_m * tiles_n;
   FusedArgs arg = a;
-  if (!a.dtrans && !a.col_cnt && tiles <= blocks) {
-    // one tile each (60 k x 4 tiles: 17 us, and 23 us with the list kernel before it)
-    arg.queue = nullptr;
-    blocks = (int)tiles;
-  } else {
-    blocks = (int)std::min<int64_t>(blocks, (tiles + 7) / 8 * 8);
+  // Lists or a workgroup per possible tile?  A tile from a list costs some 4 us of its own (heads
+  // and items are read one after the other) and the list kernel 3 to 8: lists pay where many of
+  // many tiles are empty.  Time with lists over without: 1 model of 60 k (60 tiles) 1.05, 200 of
+  // 200 k (1000) 1.15, 2 of 400 k (1600) 1.05, 40 of 400 k, l <= 3500 (11 000) 0.98, 20 of 3000 k
+  // (48 000) 0.90.  Untransposed every tile is written: 60 x 4000 x 4096 nodes 1.03, 2500 x 4000
+  // x 3000 1.12, 3000 x 1500 x 300 1.52.
+  const int64_t direct = (int64_t)(kcount + 7) / 8 * 8 * tiles_m * tiles_n;
+  if (a.dtrans && tiles > 2 * blocks) {
     hipLaunchKernelGGL(tile_list_kernel, dim3(8), dim3(256), 0, s, a, TM, TN, tiles_m, tiles_n,
                        kcount, blocks / 8);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+  } else {
+    // (a launch counts its threads in 32 bits; at most 4 columns: always enough)
+    if (direct * (64 * WR * WC) >= (int64_t)1 << 32) return hipErrorInvalidValue;
+    arg.queue = nullptr;
+    blocks = (int)direct;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * WR * WC), lds, s, arg,
                      tiles_m * tiles_n, tiles_m, kcount);
