@@ -387,7 +387,7 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
   los::SweepShape sw{};
   los::ProjectShape sh{};
   if (desc) {
-    sw = los::project_sweep_shape(nsrc, nk, ntau, env_int("LOS_PROJ_WAVES"));
+    sw = los::project_sweep_shape(nsrc, lmax - lmin + 1, nk, ntau, env_int("LOS_PROJ_WAVES"));
   } else {
     sh = los::project_fp64_shape(nsrc, ntau, env_int("LOS_PROJ_WAVES"), env_int("LOS_PROJ_SLOTS"));
     if (sh.waves == 0)
@@ -444,8 +444,9 @@ int los_project_tensor(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, int
   if (scheme && std::atoi(scheme) == 0)
     return fail(LOS_ERR_UNSUPPORTED, "los_project_tensor: needs the sweep scheme");
   // the sweep: rows lmin-1 .. lmax, columns S_P, S_P/x, S_P/x^2, S_T/x^2
-  const los::SweepShape sh = los::project_sweep_shape(4, nk, ntau, env_int("LOS_PROJ_WAVES"));
   const int nl = lmax - lmin + 1;
+  const los::SweepShape sh =
+      los::project_sweep_shape(4, nl + 1, nk, ntau, env_int("LOS_PROJ_WAVES"));
   void *ws = nullptr;
   int rc = ws_reserve(ctx, WS_TENSOR, sizeof(double) * 4 * (size_t)(nl + 1) * (size_t)nk, &ws);
   if (rc != LOS_OK) return rc;
@@ -511,7 +512,8 @@ int los_project_lsample(los_ctx *ctx, int32_t lmin, int32_t lmax, const int32_t 
     return fail(LOS_ERR_UNSUPPORTED, "los_project_lsample: needs the sweep scheme");
   const int nl = lmax - lmin + 1, nblk = (nl + 15) / 16;
   const bool every = nls == nl;  // every multipole: the dense sweep, same output
-  const los::SweepShape sh = los::project_sweep_shape(nsrc, nk, ntau, env_int("LOS_PROJ_WAVES"));
+  const los::SweepShape sh =
+      los::project_sweep_shape(nsrc, nl, nk, ntau, env_int("LOS_PROJ_WAVES"));
   // device tables (output row per multipole, sampled-row mask per 16-row
   // block), rebuilt only when the list changes
   const size_t bytes = sizeof(int32_t) * (size_t)nl + sizeof(uint32_t) * (size_t)nblk;
