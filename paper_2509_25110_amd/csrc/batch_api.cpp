@@ -105,6 +105,11 @@ void free_plan(los_batch *b) {
 // plan's key wins.  Key: architecture, pipeline, precision and buckets of the
 // shape (n_tau padded to 64, multipoles in 256s, widest row and row count in
 // powers of two); value: the fused shape index or the table tile "mb x nc".
+// The fused pipeline's name carries a version, raised when its kernels or their
+// shapes change: a choice timed on others is not applied (a plan of 48 models
+// would keep 256 x 128 tiles, 35.1 ms against 33.1).  Version 1 had no number.
+constexpr const char *kFusedTuneName = "fused2";
+
 int pow2_bucket(int64_t v) {
   int b = 0;
   while (v > 1) {
@@ -123,7 +128,7 @@ std::string tune_key(const los_batch *b, int maxcol) {
   }
   char buf[256];
   std::snprintf(buf, sizeof buf, "%s %s prec=%d ntau=%lld nl=%d col=%d rows=%d", arch.c_str(),
-                b->fused ? "fused" : "table", b->prec, (long long)((b->ntau + 63) / 64 * 64),
+                b->fused ? kFusedTuneName : "table", b->prec, (long long)((b->ntau + 63) / 64 * 64),
                 (b->nl + 255) / 256 * 256, pow2_bucket(maxcol), pow2_bucket(b->nrows));
   return buf;
 }
