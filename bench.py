@@ -68,15 +68,43 @@ def fp64_kernel():
     return "project_fp64_sweep_kernel", "project_fp64_sweep_kernel.hpp"
 
 
+def float_sweep(prec, wl):
+    """True where los_project takes float data through the FP64 sweep: LOS_FP32, unless the
+    environment asks for the matrix cores or the rows are few and long."""
+    few_long = (wl.nl >= 640 and wl.nk <= 128) or (wl.nl >= 2000 and wl.nk <= 256 and wl.ntau >= 512)
+    asked = "LOS_MIXED_FUSED" in os.environ or "LOS_FUSED_SHAPE" in os.environ
+    return prec == 1 and not few_long and not asked
+
+
+def projection_labels(prec, wl, tensor=False):
+    """(path, kernel name, dtype) of the projection that a one-model workload runs."""
+    if tensor:
+        return ("FP64 tensor-mode path (sweep of S_P, S_P/x, S_P/x^2, S_T/x^2, row combination)",
+                fp64_kernel()[0], "f64")
+    if prec == 0:
+        return "FP64 plain path", fp64_kernel()[0], "f64"
+    if float_sweep(prec, wl):
+        return ("FP64 sweep on float sources and transfer functions", "project_fp64_sweep_kernel",
+                "f64 j_l and sums, f32 data")
+    kernel = "jseed_kernel + fused_gemm_kernel"
+    if os.environ.get("LOS_MIXED_FUSED", "1").strip() == "0":
+        kernel = "jtable_kernel + mfma_gemm_kernel"
+    return {1: ("FP32 MFMA path", kernel, "f64 j_l, f32 product"),
+            2: ("split-BF16x3 MFMA path", kernel, "f64 j_l, bf16x3 product")}[prec]
+
+
 def traffic_for(prec, wl):
     """HBM bytes per projection launch from the committed counter profile of the same kernel
     source and workload (FETCH_SIZE and WRITE_SIZE, each scaled by what the counter reads for a
     plain device copy of known size); None when there is none or the source has changed."""
     import hashlib
-    if prec != 0:
+    if prec != 0 and not float_sweep(prec, wl):
         return None
     name, fname = fp64_kernel()
-    path = os.path.join(ROOT, "profiles", "%s_%s.txt" % (name.replace("_kernel", ""), wl.name))
+    name = name.replace("_kernel", "")
+    if prec != 0:
+        name, fname = "project_mixed", "project_fp64_sweep_kernel.hpp"
+    path = os.path.join(ROOT, "profiles", "%s_%s.txt" % (name, wl.name))
     src = os.path.join(ROOT, "paper_2509_25110_amd", "csrc", fname)
     if not os.path.exists(path):
         return None
@@ -773,10 +801,7 @@ def main():
                   "cl_rel_dev_vs_direct_sources": err}
         err = None  # the golden C_l are for sources given on the LOS grid itself
 
-    path = {0: "FP64 plain path", 1: "FP32 MFMA path", 2: "split-BF16x3 MFMA path"}[prec]
-    if tensor:
-        path = "FP64 tensor-mode path (sweep of S_P, S_P/x, S_P/x^2, S_T/x^2, row combination)"
-    kernel = fp64_kernel()[0] if prec == 0 else "jseed_kernel + fused_gemm_kernel"
+    path, kernel, dtype = projection_labels(prec, wl, tensor)
     out = {
         "metric": METRIC,
         "value": K / (total_ms * 1e-3),
@@ -788,7 +813,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": {0: "f64", 1: "f64 j_l, f32 product", 2: "f64 j_l, bf16x3 product"}[prec],
+        "dtype": dtype,
         "data": "synthetic",
         "config": {"workload": "%s: %s, %s%s" % (wl.name, inputs.DESCRIPTIONS[wl.name], path,
                                                  ", sources splined from %d coarse k each step"
