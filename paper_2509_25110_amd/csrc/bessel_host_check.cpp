@@ -12,6 +12,9 @@ void los_hostcheck_debye_j(int64_t n, const int32_t *l, const double *x, double 
   for (int64_t i = 0; i < n; ++i) out[i] = los::debye_j(l[i], x[i]);
 }
 
+// Largest y' = (nu - x) / (nu + x) that debye_j's polynomial for eta is fitted for.
+double los_hostcheck_eta_y_max(void) { return los::kEtaYMax; }
+
 // The seed pair of a descending sweep over lmin..lmax for each x[i] (weight 1)
 // with the FP64 band cut ltop (mfma = 0) or the MFMA paths' ltop_mfma (1):
 // R[i] = its top row (-1: none), (cur[i], nxt[i]) = (j_R, j_{R+1}).
