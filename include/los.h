@@ -141,6 +141,11 @@ int los_bessel_table(los_ctx *ctx, const double *x, int64_t nx, int32_t lmin, in
  * rows) and the product kernel regenerates each tile of J_k from it in on-chip memory,
  * multiplying in the given precision with FP32 accumulation; LOS_MIXED_FUSED=0 selects
  * whole FP32 tables in the workspace instead.  Those two give the same values.
+ * The route, and with it a k row's LOS_FP32 values, depends on how many rows the call has: the same
+ * row may differ by ~1e-6 of sum |w S j_l| between calls of different nk, and from a batch at
+ * LOS_FP32.  LOS_MIXED_FUSED=1 keeps every call on the matrix cores, where a row has the same
+ * values in every call and those of a batch.  The FP64 sums are in an order that depends on the
+ * call's shape too (rounding only, ~1e-16).
  * Errors: LOS_ERR_OOM if the workspace cannot be allocated.
  */
 int los_project(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, int64_t ntau, double tau0,
@@ -264,7 +269,7 @@ int cl_integrate_noalloc(los_ctx *ctx, const void *delta, int32_t delta_prec, in
  *
  * Errors: LOS_ERR_INVALID for NULL pointers, bad lists or sizes;
  * LOS_ERR_UNSUPPORTED when the two-pass FP64 scheme is selected
- * (LOS_PROJ_SCHEME=0) or no launch shape fits ntau.
+ * (LOS_PROJ_SCHEME=0).
  */
 int los_project_lsample(los_ctx *ctx, int32_t lmin, int32_t lmax, const int32_t *ls,
                         int32_t nls, int64_t nk, int64_t ntau, double tau0, const double *k,

@@ -317,7 +317,7 @@ struct Recon {
 // largest |C_e - cl| is divided once.
 // Bound by the FP64 exp and sinh (VALU) beside the matrix cores: 4096 rows x 4999 multipoles
 // x 4 members take 1.27 ms (1.66 ms with the library's exp and sinh; 1.22 ms with exp and sinh
-// that were less accurate than these), three waves a SIMD at the price of 24 spilled registers
+// that were less accurate than these), three waves a SIMD at the price of 23 spilled registers
 // (96 bytes of scratch a lane); two waves were 0.13 ms slower.
 template <int MEM, int WM, int WN, int NB, int KT>
 __global__ __launch_bounds__(256, 3) void reconstruct_kernel(Recon a) {

@@ -70,8 +70,6 @@ hipError_t jacobi_eig(const double *A, int q, int sweeps, double *V, double *eva
                       hipStream_t s);
 hipError_t whiten(const double *c, int64_t n, int ncomp, int s_idx, int nout, double *sigma,
                   float *z, hipStream_t s);
-hipError_t unwhiten(const float *out, int64_t n, int ncomp, int s_idx, int nout,
-                    const double *sigma, float *cz, hipStream_t s);
 // Member mean into cl and the largest deviations into err_bits (4 n words, zeroed before).
 hipError_t ensemble(const float *y, int members, int64_t n, int nl, const double *t, double *cl,
                     unsigned int *err_bits, hipStream_t s);

@@ -63,7 +63,7 @@ struct SweepShape {
   size_t lds;  // dynamic LDS bytes
 };
 SweepShape project_sweep_shape(int nsrc, int nl, int64_t nk, int64_t ntau, int force_waves = 0);
-// f32: S and delta are float (plain columns only); every sum is FP64 all the same.
+// f32: S and delta are float (plain columns only); a pass's sums are FP64 all the same.
 hipError_t project_sweep_launch(const ProjectArgs &a, int nsrc, const SweepShape &sh, bool f32,
                                 hipStream_t s);
 

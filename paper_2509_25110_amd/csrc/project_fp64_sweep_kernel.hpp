@@ -29,6 +29,8 @@
 //     any grid) is swept by groups of waves, each taking all blocks over its share of the
 //     slots; the groups' sums meet in LDS.  C2 1905 -> 1770 us, sampled 1455 -> 1355, the
 //     tensor case 988 -> 949, C3 in FP32 7.19 -> 6.83 ms.
+// The upward runs of two slots side by side in a wave's setup were 2 to 5 % slower at every size:
+// these runs are a small part of the setup.
 // Why this split: the sweep is bound by FP64 VALU issue.  With the nodes of a row
 // divided among the waves instead (each wave walking every block, the pairs in
 // registers), every wave reduces every block over its lanes, which was 30 % of the
@@ -181,7 +183,8 @@ struct SlotList {
 };
 
 // T: type of the sources and of delta (float: the sources are widened as they are
-// used, every sum is FP64, and delta is rounded once).  SMP: multipole sampling.
+// used, a pass's sums are FP64, and delta is rounded at the end of each pass, of which there
+// are as many as the launch shape gives the tau axis).  SMP: multipole sampling.
 // SC: the variant with per-column scalings (E-mode, 1/x, 1/x^2) and source planes;
 // without it every column s reads plane s unscaled.
 template <typename T, int NSRC, bool SMP, bool SC>

@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void spline_eval_kernel(const double *__restri
   const int64_t groups = (nk + ER - 1) / ER;
   const int64_t L = blockIdx.x, per = (groups + 7) / 8;
   const int64_t g = (L % 8) * per + L / 8;
-  if (g >= groups || L / 8 >= per) return;
+  if (g >= groups) return;
   const int64_t i0 = g * ER;
   const int nr = (int)min((int64_t)ER, nk - i0);
   const int lane = threadIdx.x & 63;

@@ -54,3 +54,16 @@ def test_few_long_rows(torch_dev, ctx, nk, nl, ntau, monkeypatch):  # noqa: F811
                           wl.S.astype(np.float32).astype(np.float64), with_abs=True)
     scale = np.maximum(np.max(A, axis=0, keepdims=True), 1e-300)
     assert float(np.max(np.abs(more[:nk] - got) / scale)) <= eps_for(1, ntau) + 2.0 ** -24 + 1e-10
+
+
+def test_matrix_cores_by_request_independent_of_the_call(torch_dev, ctx, monkeypatch):  # noqa: F811
+    """LOS_MIXED_FUSED=1: a k grid in two calls gives bitwise the rows of one call."""
+    import copy
+    wl = inputs.small(lmax=700, nk=150, kmax=0.1, ntau=300, nsrc=2)
+    monkeypatch.setenv("LOS_MIXED_FUSED", "1")
+    whole, _, _ = run_mixed(torch_dev, ctx, wl, 1)
+    for lo, hi in ((0, 47), (47, 150)):
+        part = copy.copy(wl)
+        part.k, part.S = wl.k[lo:hi], wl.S[:, lo:hi]
+        part.w_lnk, part.Pk = wl.w_lnk[lo:hi], wl.Pk[lo:hi]
+        np.testing.assert_array_equal(run_mixed(torch_dev, ctx, part, 1)[0], whole[lo:hi])
