@@ -29,6 +29,8 @@
 //     any grid) is swept by groups of waves, each taking all blocks over its share of the
 //     slots; the groups' sums meet in LDS.  C2 1905 -> 1770 us, sampled 1455 -> 1355, the
 //     tensor case 988 -> 949, C3 in FP32 7.19 -> 6.83 ms.
+// Scalar registers are spilled (94 to 159 by variant), all of them in the setup and between
+// blocks; 32 bytes of scratch a lane in the sampled variants.
 // The upward runs of two slots side by side in a wave's setup were 2 to 5 % slower at every size:
 // these runs are a small part of the setup.
 // Why this split: the sweep is bound by FP64 VALU issue.  With the nodes of a row
