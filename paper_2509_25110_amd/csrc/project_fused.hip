@@ -281,30 +281,31 @@ __device__ inline void tile_at(const FusedArgs &a, int ki, int tm, int tn, int l
   t.top_cap = 16 * t.lb_last + 15 - t.tile_lo;  // last tile row any column needs
 }
 
-// A workgroup's tiles (thread 0 only).  The first is its own: workgroup 8 s + x of the launch has
-// place s of list x.  The rest of list x, from place gridDim.x / 8 on, and then of the other
-// lists, are taken as they come.  A list's head is read before it is raised, and each has a cache
-// line of its own: some hundred workgroups raising one line's heads at the end made 300 us.
-// Without lists (queue nullptr) every possible tile is a workgroup, dealt to the XCDs as the lists
-// are; those past the row's columns or their l_max have nothing to do.  An XCD deals its workgroups
-// to 4 shader engines in turn: with an even number of tiles a row the same ones got every row's
-// full tiles, unless the order turns with the row (l <= 2500, 4000 k, 3000 nodes, 3 sources: 3.36 ->
-// 2.86 ms, l <= 1000, 3000 k, 500 nodes: 490 -> 278 us).
+// Without lists every possible tile is a workgroup, dealt to the XCDs as the lists are; those past
+// the row's columns or their l_max (y = -1) have nothing to do.  An XCD deals its workgroups to 4
+// shader engines in turn: with an even number of tiles a row the same ones got every row's full
+// tiles, unless the order turns with the row (l <= 2500, 4000 k, 3000 nodes, 3 sources: 3.36 -> 2.86
+// ms, l <= 1000, 3000 k, 500 nodes: 490 -> 278 us; a kernel of its own, without the lists' loop: 2.79
+// ms and 262 us, l <= 3000, 1500 k, 300 nodes 263 -> 239).
 template <int TM, int TN>
-__device__ inline int2 first_tile(const FusedArgs &a, int per_row, int tiles_m, int kcount,
-                                  int &from) {
+__device__ inline int2 direct_tile(const FusedArgs &a, int per_row, int tiles_m, int kcount) {
   const int x = blockIdx.x & 7, s = blockIdx.x >> 3;
-  if (!a.queue) {
-    from = 8;
-    const int row = s / per_row, pos = (s + (per_row & 1 ? 0 : row >> 1)) % per_row;
-    const int ki = kcount - 1 - x - 8 * row, u = pos % tiles_m, tn = pos / tiles_m;
-    if (ki < 0) return make_int2(0, -1);
-    const int64_t r = a.k0 + ki;
-    if (tn * TN >= (a.col_cnt ? a.col_cnt[r] : a.ncol) ||
-        u * (TM / 16) > last_block(a, r, tn * TN))
-      return make_int2(0, -1);
-    return make_int2((int)((unsigned)u << 16 | ki), tn);
-  }
+  const int row = s / per_row, pos = (s + (per_row & 1 ? 0 : row >> 1)) % per_row;
+  const int ki = kcount - 1 - x - 8 * row, u = pos % tiles_m, tn = pos / tiles_m;
+  if (ki < 0) return make_int2(0, -1);
+  const int64_t r = a.k0 + ki;
+  if (tn * TN >= (a.col_cnt ? a.col_cnt[r] : a.ncol) || u * (TM / 16) > last_block(a, r, tn * TN))
+    return make_int2(0, -1);
+  return make_int2((int)((unsigned)u << 16 | ki), tn);
+}
+
+// A workgroup's tiles from the lists (thread 0 only).  The first is its own: workgroup 8 s + x of
+// the launch has place s of list x.  The rest of list x, from place gridDim.x / 8 on, and then of
+// the other lists, are taken as they come.  A list's head is read before it is raised, and each
+// has a cache line of its own: some hundred workgroups raising one line's heads at the end made
+// 300 us.
+__device__ inline int2 first_tile(const FusedArgs &a, int64_t per_row, int kcount, int &from) {
+  const int x = blockIdx.x & 7, s = blockIdx.x >> 3;
   if (s < a.queue[kQueueStride * x + 1]) return a.items[list_base(x, kcount) * per_row + s];
   from = 8;  // list x has no more than one tile for each of its workgroups
   return make_int2(0, -1);
@@ -617,9 +618,9 @@ __device__ inline void store_acc(const FusedArgs &a, const Tile &t, const f4 (&a
 // (interleaved, so that the waves share a tile's partly filled upper blocks) by every WC-th
 // column block from wc on; the next chunk's inputs load meanwhile.  The waves of one wr are on
 // one SIMD (w and w + 4), so that any number of column blocks is shared evenly.
-// With lists the workgroups stay and take tiles until these are empty; the list
-// position of the next tile is fetched during the current one.
-template <int PREC, int WR, int WC, int NB, bool TINY>
+// LISTS: the workgroups stay and take tiles from the lists until these are empty; the list
+// position of the next tile is fetched during the current one.  Otherwise each has one tile.
+template <int PREC, int WR, int WC, int NB, bool TINY, bool LISTS>
 __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kernel(FusedArgs a, int per_row,
                                                                   int tiles_m, int kcount) {
   constexpr int NT = 64 * WR * WC, TM = 32 * WR, TN = 16 * NB * WC;
@@ -635,15 +636,20 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kern
   const int tail = TINY ? 0 : (int)(-a.ntau & 3), ctail = (int)(a.ntau / KB);
   int from = 0;
   int2 item = make_int2(0, -1);
-  if (tid == 0) item = first_tile<TM, TN>(a, per_row, tiles_m, kcount, from);
+  if (!LISTS || tid == 0) {
+    if constexpr (LISTS) item = first_tile(a, per_row, kcount, from);
+    else item = direct_tile<TM, TN>(a, per_row, tiles_m, kcount);
+  }
   for (;;) {
-    if (tid == 0) s_item = item;
-    __syncthreads();
-    const unsigned mk = __builtin_amdgcn_readfirstlane(s_item.x);
-    const int tn = __builtin_amdgcn_readfirstlane(s_item.y);
+    if constexpr (LISTS) {
+      if (tid == 0) s_item = item;
+      __syncthreads();
+    }
+    const unsigned mk = __builtin_amdgcn_readfirstlane(LISTS ? s_item.x : item.x);
+    const int tn = __builtin_amdgcn_readfirstlane(LISTS ? s_item.y : item.y);
     if (tn < 0) return;
     const int ki = mk & 0xffff;
-    if (tid == 0) item = next_tile(a, per_row, kcount, from);
+    if (LISTS && tid == 0) item = next_tile(a, per_row, kcount, from);
     Tile t;
     int need;
     tile_at<TM, TN>(a, ki, mk >> 16, tn, lane, t, need);
@@ -652,7 +658,7 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kern
     int last_blk = t.lb_last;
     if (a.dtrans) {
       int top;
-      if (a.queue) {
+      if (LISTS) {
         top = a.rowtop[ki];
       } else {  // no list kernel has left it: the row's first tile does
         top = wave_max_int(max(ch.cm0, ch.cm1));
@@ -672,7 +678,7 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kern
     ChunkIn<SPieces<TN, NT>::SPT> in;
     int c = next_chunk(ch.act0, ch.act1, 0);
     if (c >= 0) load_chunk_in<TN, NT, TINY>(a, t, p, c, lane, tid, in);
-    __syncthreads();  // s_item is read
+    if (LISTS) __syncthreads();  // s_item is read
     while (c >= 0) {
       const int top_tr = chunk_top(a, t, ch, c);
       if (wc == 0 && p.seg_ok && 32 * wr <= top_tr) gen_segment(a, p, in, 32 * wr, lane, sm);
@@ -692,7 +698,7 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 2 ? 4 : 1) void fused_gemm_kern
       c = cn;
     }
     store_acc<WR, WC, NB>(a, t, acc, njb, last_blk, wr, wc, g, r16);
-    if (!a.queue) return;
+    if (!LISTS) return;
   }
 }
 
@@ -732,39 +738,42 @@ hipError_t launch_fused_t(const FusedArgs &a, int kcount, int max_ncol, hipStrea
   const int tiles_m = (a.nlb * 16 + TM - 1) / TM, tiles_n = (max_ncol + TN - 1) / TN;
   if (kcount < 1 || max_ncol < 1 || kcount > 65535 || tiles_m > 65535) return hipErrorInvalidValue;
   const size_t lds = LdsLayout<PREC>::bytes(TM, TN);
-  auto kern = fused_gemm_kernel<PREC, WR, WC, NB, TINY>;
+  auto kern = fused_gemm_kernel<PREC, WR, WC, NB, TINY, true>;
   static Resident resident;
   int blocks = 0;
   hipError_t e = resident_blocks(kern, 64 * WR * WC, lds, resident, blocks);
   if (e != hipSuccess) return e;
   const int64_t tiles = (int64_t)kcount * tiles_m * tiles_n;
-  FusedArgs arg = a;
   // Lists or a workgroup per possible tile?  A tile from a list costs some 4 us of its own (heads
   // and items are read one after the other) and the list kernel 3 to 8: lists pay where many of
   // many tiles are empty.  Time with lists over without: 1 model of 60 k (60 tiles) 1.05, 200 of
   // 200 k (1000) 1.15, 2 of 400 k (1600) 1.05, 40 of 400 k, l <= 3500 (11 000) 0.98, 20 of 3000 k
-  // (48 000) 0.90.  Untransposed every tile is written: 60 x 4000 x 4096 nodes 1.03, 2500 x 4000
-  // x 3000 1.12, 3000 x 1500 x 300 1.52.
-  const int64_t direct = (int64_t)(kcount + 7) / 8 * 8 * tiles_m * tiles_n;
+  // (48 000) 0.90.  Untransposed every tile is written: 60 x 4000 x 4096 nodes 1.04, 2500 x 4000
+  // x 3000 1.14, 3000 x 1500 x 300 1.66.
   if (a.dtrans && tiles > 2 * blocks) {
     hipLaunchKernelGGL(tile_list_kernel, dim3(8), dim3(256), 0, s, a, TM, TN, tiles_m, tiles_n,
                        kcount, blocks / 8);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else {
+    const int64_t direct = (int64_t)(kcount + 7) / 8 * 8 * tiles_m * tiles_n;
     // (a launch counts its threads in 32 bits; at most 4 columns: always enough)
     if (direct * (64 * WR * WC) >= (int64_t)1 << 32) return hipErrorInvalidValue;
-    arg.queue = nullptr;
     blocks = (int)direct;
+    kern = fused_gemm_kernel<PREC, WR, WC, NB, TINY, false>;
+    static Resident attributes;  // (the large-LDS limit of this kernel)
+    int unused = 0;
+    e = resident_blocks(kern, 64 * WR * WC, lds, attributes, unused);
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * WR * WC), lds, s, arg,
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * WR * WC), lds, s, a,
                      tiles_m * tiles_n, tiles_m, kcount);
   return hipGetLastError();
 }
 
-// Registers spilled: 128 x 128 tiles 3 (16 bytes a lane, the price of 4 waves a SIMD); 256 x 256 2 in
-// FP32 and 75 (304 bytes) in split-BF16x3, where the batch tuner times it all the same (C4 takes
-// 128 x 128).
+// Registers spilled: with lists, 128 x 128 tiles 1 (the price of 4 waves a SIMD); 256 x 256 1 in FP32
+// and 73 (296 bytes a lane) in split-BF16x3, where the batch tuner times it all the same and finds
+// it 3 times slower on C4.
 template <int PREC>
 hipError_t launch_fused_p(const FusedArgs &a, int shape, int kcount, int max_ncol,
                           hipStream_t s) {
