@@ -388,14 +388,14 @@ int autotune_fused(los_batch *b, const SolveArgs &s, hipStream_t st) {
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
   if (rc != LOS_OK) return rc;
-  float best = 1e30f;
+  // Another shape than 128 x 128 has to be 3 % faster: near ties on the two chunks are not ties over
+  // all (C4 in split-BF16x3: 256 x 128 18.05 ms against 18.22 there, the step 74.4 against 69.7).
+  int best = 0;
   for (int i = 0; i < kWide; ++i) {
     b->ftune_ms[wide[i]] = total[i];
-    if (total[i] < best) {
-      best = total[i];
-      b->fshape = wide[i];
-    }
+    if (total[i] < total[best] * (best == 0 ? 0.97f : 1.f)) best = i;
   }
+  b->fshape = wide[best];
   b->tuned = true;
   cache_store(b);
   return LOS_OK;
