@@ -350,12 +350,12 @@ int los_project_kernels(los_ctx *ctx, int32_t lmin, int32_t lmax, int64_t nk, in
   // Mixed precision: float sources and delta.  A k row has at most 4 columns, of which the
   // matrix cores use 16 at a time and for which they need every Bessel value generated, rounded
   // and staged, so for LOS_FP32 the FP64 sweep takes these too (widening the sources as it
-  // reads them): C3 6.4 ms against 16.7 ms on the matrix cores, and no workspace.  A sweep's
+  // reads them): C3 6.4 ms against 16.5 ms on the matrix cores, and no workspace.  A sweep's
   // rows are whole workgroups, though, each a chain of blocks of multipoles: few and long rows
   // go to the matrix cores, whose tiles cut them.  3 columns, lmax 1000, 120 k, 1000 nodes: 77 us
-  // by the sweep, 67 on the matrix cores (250 k: 77, 83; lmax 300, 30 k: 33, 44); lmax 3000, 60 k,
-  // 150 nodes: 105, 71; 250 k, 1000 nodes: 198, 150; 150 nodes: 105, 91; 500 k, 4000 nodes: 634,
-  // 617; 800 k, 300 nodes: 155, 174.  (1 column: 57, 67; 96, 70; 143, 149.)
+  // by the sweep, 65 on the matrix cores (250 k: 77, 83; lmax 300, 30 k: 33, 43); lmax 3000, 60 k,
+  // 150 nodes: 105, 70; 250 k, 1000 nodes: 199, 145; 150 nodes: 105, 87; 500 k, 4000 nodes: 634,
+  // 607; 800 k, 300 nodes: 155, 161.  (1 column: 57, 65; 96, 70; 142, 145.)
   // LOS_BF16X3 names the split product itself, whose values a batch at that precision has to
   // match, and stays on the matrix cores.  LOS_MIXED_FUSED or LOS_FUSED_SHAPE in the
   // environment select the matrix-core pipelines for both.
